@@ -28,27 +28,44 @@
 //    they are deterministic.  Small batches, whose even share would fall
 //    below eight blocks, instead cut every segment into equal block-aligned
 //    pieces, one per workgroup, so that no workgroup straddles two segments.
-//  * K/V stream through an LDS ring of three 32-key blocks.  Each wave
-//    loads one 4 KiB tile per block (one page's K or V) into registers
-//    three blocks ahead, as four contiguous 1 KiB loads from a scalar page
-//    address, and writes it to the ring when its block comes up; on gfx950
+//  * K/V stream through an LDS ring of three 32-key stages.  Each wave
+//    loads one 4 KiB tile per stage (one page's K or V) into registers
+//    three stages ahead, as four contiguous 1 KiB loads from a scalar page
+//    address, and writes it to the ring when its stage comes up; on gfx950
 //    this sustains more bandwidth than LDS-direct loads.  Page ids are
 //    staged in LDS per piece.
 //  * Transposed scores: S^T = K Q^T and O^T = V^T P^T with
 //    v_mfma_f32_16x16x32_bf16.  The score tile comes out with one query row
-//    per lane column, which is exactly the B-operand layout the PV product
-//    needs, so P never crosses lanes; the row max and the row sum each need
-//    two row-swap permutes.  Each weight enters PV as a hi + lo pair of bf16
-//    values (two MFMAs per output tile), so the weights carry about 2^-17
-//    of their value and the output's own bf16 rounding dominates the error.
+//    per lane column, which after two row-swap permutes a register pair is
+//    exactly the B-operand layout the PV product needs.  Each weight enters
+//    PV as a hi + lo pair of bf16 values (two MFMAs per output tile), so the
+//    weights carry about 2^-17 of their value and the output's own bf16
+//    rounding dominates the error.
 //  * Lazy rescaling: the running maximum only moves (and the accumulators
-//    are only rescaled) when a block's maximum exceeds it by more than a
+//    are only rescaled) when a key's score exceeds it by more than a
 //    factor 2^8, which keeps the weights below 2^8.  It is kept an integer,
 //    so rescales and merge weights are exact powers of two.
 //  * Waves of a workgroup split the dims when a request has one or two row
-//    tiles; with three or more row tiles each wave owns tiles.
+//    tiles; beyond that each wave owns one or two tiles, so that every piece
+//    reads its K and V once: four waves hold the eight tiles of eight query
+//    heads to a KV head and a full block, eight waves the sixteen of G = 16.
 //  * The workgroup placed second on a CU runs at raised wave priority over
-//    most of its share, so that both workgroups of a CU finish together.
+//    half of its share, so that both workgroups of a CU finish together.
+//
+// What bounds it, and what it measured (MI355X, split + combine kernels, us a
+// call; before: each wave held one tile, so that more than four took a pass of
+// K and V for every four, and a step's softmax took 132 vector instructions to
+// a tile where it now takes about 60):
+//   B=32, 32 query / 8 KV heads, contexts to 8K (0.6 GB): HBM; 105.7 -> 104.1,
+//     5.8 TB/s
+//   B=32, 64 / 8 heads, lengths about 8, contexts to 16K (1.2 GB): HBM, with
+//     the vector units close behind; 343 -> 228, 5.3 TB/s
+//   B=24, 32 / 2 heads, full blocks, contexts to 6K: the matrix and vector
+//     units (16 tiles to a key), then 33 MB of partials; 104 -> 62
+//   B=32, head_dim 64, contexts to 8K (0.3 GB): HBM; 60.7 -> 59.0
+//   B=8, full blocks, contexts to 2K (40 MB): the chain from launch to the
+//     last block; 23.4 -> 22.0
+//   B=1, full block, context 700 (3 MB): the same; 16.9 -> 15.9
 #include "dsv_internal.h"
 
 #include <math.h>
@@ -56,8 +73,6 @@
 namespace dsv {
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kWaves = kThreads / kWave;
 // Combine kernel: 1024-thread workgroups (32 rows at D = 128) need a quarter
 // of the workgroups that 256 threads do, most of which exit at once; measured
 // 0.6 us faster at B=32 with contexts up to 8K (Qwen3-8B attention shape).
@@ -76,23 +91,25 @@ constexpr int kMinShare = 8 * kBlockKeys;
 constexpr int kLeadKeys = kAttnLeadKeys;
 // Wave priority.  The persistent grid holds two workgroups per CU, and the
 // one the dispatcher places second (grid index >= number of CUs) loses
-// instruction arbitration to the older first one: with equal shares it
-// finished several microseconds later, and the CU's last stretch ran on one
-// workgroup.  Its waves therefore run at raised priority until kBoostPct
-// percent of its share is done, then at the default.  Priority changes no
-// arithmetic.  Drop points of 50, 65, 80 and 90 percent and the whole share
-// were compared; 65 gained the most over shapes.
-constexpr int kBoostPct = 65;
+// instruction arbitration to the older first one: with equal shares and no
+// priorities the first ended at 66 us and the second at 91 (B=32, contexts up
+// to 8K).  Its waves therefore run at raised priority until kBoostPct percent
+// of its share is done, then at the default, and both end at about 90 us.
+// Priority changes no arithmetic.  Drop points, B=32 contexts to 8K / eight
+// query heads to a KV head and contexts to 16K, us a call: 50% 104.2 / 226.7,
+// 65% 104.4 / 228.8, 80% 106.1 / 229.6, none 113 / 244.
+constexpr int kBoostPct = 50;
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) {
   return __builtin_bit_cast(bf16x8, v);
 }
 
-// Two bf16 -> one uint32 (low half first), round to nearest even.
+// Two bf16 -> one uint32 (low half first), round to nearest even: one
+// v_cvt_pk_bf16_f32 (two scalar conversions compile to four instructions).
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-  __bf16 a = (__bf16)lo, b = (__bf16)hi;
-  return (uint32_t)__builtin_bit_cast(uint16_t, a) |
-         ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){lo, hi}, bf16x2));
 }
 
 __device__ __forceinline__ int round_up_block(int x) {
@@ -132,94 +149,30 @@ __device__ __forceinline__ ReqMeta load_req(const AttnParams &p, int i) {
   return r;
 }
 
-// ------------------------------------------------------------------ LDS ring
-// One 32-key block (two pages) in LDS: the K tiles of both pages, then their
-// V tiles, each tile as D/32 chunks of 1 KiB.  Wave w stages page w & 1's K
-// (waves 0-1) or V (waves 2-3) tile of every block.  Lane l writes the 16
-// bytes at offset 16*l of each chunk and loads a swizzled 16-byte unit of
-// it (each aligned group of four lanes still reads one aligned 64-byte
-// piece), chosen so that the MFMA operand reads are free of LDS bank
-// conflicts for any grouping of 8, 16 or 32 lanes per LDS cycle (k_unit /
-// v_unit below).
+// -------------------------------------------------------------------- steps
+// The block loop works in steps of 32 keys (D = 128; 64 at D = 64), page pairs
+// whose tiles hold exactly the MFMA operands:
+//  K: the 1 KiB chunk c of a page's K tile is the A operand of the score
+//     MFMA over dims 32c .. 32c+31, lane l holding slot l & 15.
+//  V: lane (kq, m) of d block u takes the 16 bytes of dim 16u+m that hold
+//     slots 8*(kq>>1) .. +7 of page kq & 1 of a pair.
+constexpr int kSubKeys = 8192;              // keys whose page ids are staged at a time
+constexpr int kSubPages = kSubKeys / kPage;
+
 template <int D>
-struct Ring {
-  static constexpr int kChunks = D / 32;               // 1 KiB chunks per tile
-  static constexpr int kKRegion = 2 * kChunks * 1024;  // K tiles of both pages
-  static constexpr int kStage = 2 * kKRegion;          // 16 KiB at D = 128
-  static constexpr int kKOps = 2 * kChunks;            // K operand tiles per block
+struct Step {
+  static constexpr int kPairs = 128 / D;              // page pairs
+  static constexpr int kKeys = kBlockKeys * kPairs;   // keys
+  static constexpr int kPages = 2 * kPairs;
 };
-// Ring stages = blocks in flight in registers.  Four (16 more VGPRs, 64 KiB
-// of ring) measured 1-3% slower than three at every shape.
-constexpr int kStages = 3;
-constexpr int kSubPages = 512;  // page ids staged in LDS at a time (8192 keys)
-
-// The wave's share of one block: one page's K or V tile (D/32 chunks of
-// 1 KiB), loaded into registers (lane l holds the swizzled unit it will
-// write at offset 16*l of each chunk) and later written to its ring stage.
 template <int D>
-struct StageRegs {
-  u32x4 x[D / 32];
+struct KRegs {
+  u32x4 x[Step<D>::kPages][D / 32];  // [page][chunk]
 };
-
-template <int D>
-__device__ __forceinline__ void stage_load(const char *tile, uint32_t voff, StageRegs<D> &r) {
-#pragma unroll
-  for (int c = 0; c < D / 32; ++c)
-    r.x[c] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(tile + voff + 1024 * c));
-}
-
-template <int D>
-__device__ __forceinline__ void stage_store(char *dst, int lane, const StageRegs<D> &r) {
-#pragma unroll
-  for (int c = 0; c < D / 32; ++c)
-    *reinterpret_cast<u32x4 *>(dst + 1024 * c + 16 * lane) = r.x[c];
-}
-
-// Key order inside a block.  Row m of score half hh holds key
-// 8*(m/4) + 4*hh + m%4, so after S^T = K Q^T the lane with k-group kq holds
-// keys 8*kq + [0..7] of its query row: exactly the order the PV product
-// contracts over, and V's operand for that lane is 8 consecutive keys of one
-// dim, one 16-byte unit of the d-major V tile.
-__device__ __forceinline__ int score_key(int hh, int m) { return 8 * (m >> 2) + 4 * hh + (m & 3); }
-
-// Swizzles.  K chunk of page p: global unit u (d-chunk u/16, slot u%16)
-// sits at LDS unit k_unit(u, p) (an involution).  V chunk: global unit
-// u = 2*dim + half sits at LDS unit v_unit(u); v_unit_inv is its inverse.
-__device__ __forceinline__ int k_unit(int u, int p) { return u ^ (4 * (p ^ ((u >> 3) & 1))); }
-__device__ __forceinline__ int v_sel(int k) { return ((k >> 1) ^ (k >> 2)) & 1; }
-__device__ __forceinline__ int v_unit(int u) {
-  const int k = u >> 2, j = (u >> 1) & 1, b = u & 1;
-  return 4 * k + 2 * (b ^ v_sel(k)) + j;
-}
-__device__ __forceinline__ int v_unit_inv(int l) {
-  const int k = l >> 2, j = l & 1, b = ((l >> 1) & 1) ^ v_sel(k);
-  return 4 * k + 2 * j + b;
-}
-
-// Per-lane LDS byte offsets (within a stage) of the MFMA operands.
-struct RingLane {
-  uint32_t k0, k1;  // K operand, score half 0 / 1, chunk 0 (chunk c at +1024c)
-  uint32_t v;       // V operand of d block 0 (d block e at +512e)
+template <int D, int NE>
+struct VRegs {
+  u32x4 x[Step<D>::kPairs][NE];  // [page pair][d block]
 };
-
-template <int D>
-__device__ __forceinline__ RingLane ring_lane(int lane) {
-  using R = Ring<D>;
-  const int kgrp = lane >> 4, m = lane & 15;
-  RingLane r;
-  {
-    const int key0 = score_key(0, m), key1 = score_key(1, m);
-    const int p0 = key0 >> 4, p1 = key1 >> 4;
-    r.k0 = (uint32_t)(p0 * R::kChunks * 1024 + 16 * k_unit(kgrp * 16 + (key0 & 15), p0));
-    r.k1 = (uint32_t)(p1 * R::kChunks * 1024 + 16 * k_unit(kgrp * 16 + (key1 & 15), p1));
-  }
-  {
-    // dim m of d block 0, keys 8*(kgrp&1) .. +7 of page kgrp>>1
-    const int pv = kgrp >> 1;
-    r.v = (uint32_t)(R::kKRegion + pv * R::kChunks * 1024 + 16 * v_unit(2 * m + (kgrp & 1)));
-  }
-  return r;
-}
 
 // Maximum / sum over the four lanes that hold one query row (lanes n, n+16,
 // n+32, n+48), with the gfx950 row-swap permutes.
@@ -243,171 +196,26 @@ __device__ __forceinline__ float row_sum4(float x) {
 // more than this (base-2 units): weights then stay below 2^8, and the
 // accumulators are rescaled only on such a jump instead of every block.
 // The maximum is kept an integer (the block maximum rounded up), so every
-// rescale factor and every merge weight of the combine is an exact power of
-// two: where a segment is cut, or which rows share its tile, moves a row's
-// weights and sums by powers of two only, and its result changes only
-// through fp32 summation order.
+// rescale factor and every merge weight, in the workgroup and in the combine,
+// is an exact power of two: where a segment is cut, or which rows share its
+// tile, moves a row's weights and sums by powers of two only, and its result
+// changes only through fp32 summation order.
 constexpr float kRescaleSlack = 8.f;
+// Running maximum of a row that has seen no key yet: finite, so that no
+// difference of two of them is a NaN.
+constexpr float kNoMax = -3.402823466e38f;
 
-// Online-softmax state of one lane: one query row (lane & 15); `l` holds
-// the row sum of the weights (the same value in the row's four lanes);
-// for each of the wave's d blocks u (dims 16*(e_lo+u) + 4*(lane>>4) +
-// [0..3]), the 4 accumulated outputs.
-template <int D>
+// Online-softmax state of one wave, for TW row tiles and NE d blocks.  A lane
+// holds one query row (lane & 15) of each tile: its running maximum, its own
+// lane's share of the sum of the weights (the row's four lanes are added at
+// the end), and for each d block u the outputs of dims 16u + 4*(lane>>4) +
+// [0..3] from the wave's first d block on.
+template <int TW, int NE>
 struct RowState {
-  float m;
-  float l;
-  f32x4 o[D / 16];
+  float m[TW];
+  float l[TW];
+  f32x4 o[TW][NE];
 };
-
-// One 32-key block from ring stage byte offset `so`: scores for the wave's
-// row tile, online softmax, and the PV product for the wave's NE d blocks
-// starting at e_lo (`vb` already points at e_lo).  `full` (uniform) says every
-// key of the block is visible to every live row, so no masking is needed.
-template <int D, int NE>
-__device__ __forceinline__ void ring_compute(const char *ring, uint32_t so, const RingLane &rl,
-                                             uint32_t vb, int lane, int t0, int key_end,
-                                             int row_limit, bool full,
-                                             const bf16x8 (&qv)[D / 32], float scale_log2,
-                                             RowState<D> &st) {
-  using R = Ring<D>;
-  const int kq = lane >> 4;
-  uint4 kop[R::kKOps];
-#pragma unroll
-  for (int c = 0; c < R::kChunks; ++c) {
-    kop[c] = *reinterpret_cast<const uint4 *>(ring + so + rl.k0 + 1024 * c);
-    kop[R::kChunks + c] = *reinterpret_cast<const uint4 *>(ring + so + rl.k1 + 1024 * c);
-  }
-  uint4 vop[NE];
-#pragma unroll
-  for (int u = 0; u < NE; ++u) vop[u] = *reinterpret_cast<const uint4 *>(ring + so + vb + 512 * u);
-  f32x4 s[2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    s[h] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int c = 0; c < D / 32; ++c)
-      s[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kop[h * (D / 32) + c]), qv[c],
-                                                     s[h], 0, 0, 0);
-  }
-  // element (h, q) of this lane is key t0 + 8kq + 4h + q; raw scores (the
-  // scale is positive and applied inside the exponent)
-  float sc[2][4];
-  if (full) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) sc[h][q] = s[h][q];
-  } else {
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int t = t0 + 8 * kq + 4 * h + q;
-        const bool vis = t <= row_limit && t < key_end;
-        sc[h][q] = vis ? s[h][q] : -INFINITY;
-      }
-  }
-  float bmax = fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])),
-                     fmaxf(fmaxf(sc[1][0], sc[1][1]), fmaxf(sc[1][2], sc[1][3])));
-  bmax = row_max4(bmax) * scale_log2;
-  if (__builtin_amdgcn_ballot_w64(bmax > st.m + kRescaleSlack) != 0) {
-    const float m_new = fmaxf(st.m, ceilf(bmax));
-    // 0 on a row's first visible block, 1 for a row that still sees nothing
-    const float alpha = __builtin_amdgcn_exp2f(st.m - (m_new == -INFINITY ? 0.f : m_new));
-    st.l *= alpha;
-#pragma unroll
-    for (int u = 0; u < NE; ++u) st.o[u] *= alpha;
-    st.m = m_new;
-  }
-  const float neg_m = st.m == -INFINITY ? 0.f : -st.m;
-  // P enters the bf16 PV product as a pair: hi = P rounded to bf16 and
-  // lo = the remainder rounded to bf16, so hi + lo carries P to about 2^-17
-  // of its value and the weights add no error next to the output's own bf16
-  // rounding.  The row sum adds the fp32 weights themselves: the lane's
-  // eight, then across the row's four lanes.
-  uint32_t pk[4], pl[4];
-  float psum = 0.f;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    float pw[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      pw[q] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[h][q], scale_log2, neg_m));
-    psum += (pw[0] + pw[1]) + (pw[2] + pw[3]);
-#pragma unroll
-    for (int w = 0; w < 2; ++w) {
-      const uint32_t hi = pack_bf16x2(pw[2 * w], pw[2 * w + 1]);
-      pk[2 * h + w] = hi;
-      pl[2 * h + w] = pack_bf16x2(pw[2 * w] - __uint_as_float(hi << 16),
-                                  pw[2 * w + 1] - __uint_as_float(hi & 0xFFFF0000u));
-    }
-  }
-  const bf16x8 pb = as_bf16x8(make_uint4(pk[0], pk[1], pk[2], pk[3]));
-  const bf16x8 pbl = as_bf16x8(make_uint4(pl[0], pl[1], pl[2], pl[3]));
-  // V element q of this lane is key t0 + 8kq + q.  Keys at or past key_end
-  // may hold anything (even NaN): zero their V so that 0 * V stays 0.
-  if (!full) {
-    const int tb = t0 + 8 * kq;
-    uint32_t vmask[4];
-#pragma unroll
-    for (int w = 0; w < 4; ++w)
-      vmask[w] = (tb + 2 * w < key_end ? 0x0000FFFFu : 0u) |
-                 (tb + 2 * w + 1 < key_end ? 0xFFFF0000u : 0u);
-#pragma unroll
-    for (int u = 0; u < NE; ++u) {
-      vop[u].x &= vmask[0];
-      vop[u].y &= vmask[1];
-      vop[u].z &= vmask[2];
-      vop[u].w &= vmask[3];
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < NE; ++u)
-    st.o[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vop[u]), pb, st.o[u], 0, 0, 0);
-#pragma unroll
-  for (int u = 0; u < NE; ++u)
-    st.o[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vop[u]), pbl, st.o[u], 0, 0, 0);
-  st.l += row_sum4(psum);
-}
-
-// Writes a finished row tile for the wave's `ne` d blocks from e_lo: bf16
-// output when the piece is the whole segment, otherwise the fp32 partial in
-// this workgroup's slot (0: the segment where its share starts, 1: where it
-// ends).  (m, l) are identical in every wave of a row tile; the wave that
-// owns d block 0 writes them.
-template <int D>
-__device__ __forceinline__ void write_tile(const AttnParams &p, int g, bool complete, int slot,
-                                           const ReqMeta &rq, int rt, int e_lo, int ne,
-                                           int lane, float l, const RowState<D> &st) {
-  const int kq = lane >> 4, n = lane & 15;
-  const int rr = rt * 16 + n;
-  if (rr >= p.group * rq.k) return;
-  const int lg = __builtin_ctz(p.group);
-  const int j = rr >> lg, hh = rr & (p.group - 1);
-  if (complete) {
-    const size_t row = (size_t)(rq.q0 + j) * p.hq + (size_t)g * p.group + hh;
-    const float inv = 1.f / l;
-    uint16_t *o = p.out + row * D + 16 * e_lo + 4 * kq;
-#pragma unroll
-    for (int u = 0; u < D / 16; ++u) {
-      if (u >= ne) break;
-      uint2 w;
-      w.x = pack_bf16x2(st.o[u][0] * inv, st.o[u][1] * inv);
-      w.y = pack_bf16x2(st.o[u][2] * inv, st.o[u][3] * inv);
-      *reinterpret_cast<uint2 *>(o + 16 * u) = w;
-    }
-  } else {
-    const size_t prow = ((size_t)blockIdx.x * 2 + slot) * (p.group * kMaxQlen) + rr;
-    float *o = p.part_o + prow * D + 16 * e_lo + 4 * kq;
-#pragma unroll
-    for (int u = 0; u < D / 16; ++u) {
-      if (u >= ne) break;
-      *reinterpret_cast<f32x4 *>(o + 16 * u) = st.o[u];
-    }
-    if (kq == 0 && e_lo == 0) p.part_ml[prow] = make_float2(st.m, l);
-  }
-}
 
 // This workgroup's share of the flattened work: [start, end) in units of
 // keys over the segments laid end to end (request-major, then KV head).
@@ -474,6 +282,7 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
 
 // Block-wide exclusive scan of one value per thread: the wave scan, then the
 // wave totals through LDS (`tot` receives the block total).
+template <int NW>
 __device__ __forceinline__ int block_excl_scan(int v, int *lds_tot, int &tot) {
   const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
   const int incl = wave_incl_scan(v);
@@ -482,7 +291,7 @@ __device__ __forceinline__ int block_excl_scan(int v, int *lds_tot, int &tot) {
   int before = 0;
   tot = 0;
 #pragma unroll
-  for (int w = 0; w < kWaves; ++w) {
+  for (int w = 0; w < NW; ++w) {
     before += w < wave ? lds_tot[w] : 0;
     tot += lds_tot[w];
   }
@@ -493,9 +302,11 @@ __device__ __forceinline__ int block_excl_scan(int v, int *lds_tot, int &tot) {
 // lengths (each thread owns a contiguous run of requests): a stream-K share
 // of the flattened work, or, for small batches, one piece of one segment.
 // Workgroup 0 also publishes the per-request prefixes and the plan for the
-// combine kernel.  LDS use: lds[0..2*kWaves) scan totals, then the located
+// combine kernel.  LDS use: lds[0..2*NW) scan totals, then the located
 // share.
+template <int NW>
 __device__ Share plan_share(const AttnParams &p, int *lds) {
+  constexpr int kThreads = NW * kWave;
   const int B = p.num_reqs, tid = threadIdx.x;
   const int per = (B + kThreads - 1) / kThreads;
   const int lo = min(B, tid * per), hi = min(B, lo + per);
@@ -515,8 +326,8 @@ __device__ Share plan_share(const AttnParams &p, int *lds) {
     for (int i = lo; i < hi; ++i) sum += segment_len(p, i);
   }
   int total;
-  const int excl = block_excl_scan(sum, lds, total);  // keys before my requests
-  int *loc = lds + 2 * kWaves;  // located share: i, g, off, q0, q1, ctx, start, end
+  const int excl = block_excl_scan<NW>(sum, lds, total);  // keys before my requests
+  int *loc = lds + 2 * NW;  // located share: i, g, off, q0, q1, ctx, start, end
   const int work = total * p.hkv;
   int share = (work + (int)gridDim.x - 1) / (int)gridDim.x;
   share = max(kMinShare, round_up_block(share));
@@ -533,12 +344,12 @@ __device__ Share plan_share(const AttnParams &p, int *lds) {
 #pragma unroll
       for (int c = 0; c < kNumPieceCaps; ++c) cnt[c] += seg_pieces(seg, piece_cap(c));
     }
-    int *red = loc + 8;  // [kNumPieceCaps][kWaves]
+    int *red = loc + 8;  // [kNumPieceCaps][NW]
     const int lane = tid % kWave, wave = tid / kWave;
 #pragma unroll
     for (int c = 0; c < kNumPieceCaps; ++c) {
       const int v = wave_incl_scan(cnt[c]);
-      if (lane == kWave - 1) red[c * kWaves + wave] = v;
+      if (lane == kWave - 1) red[c * NW + wave] = v;
     }
     __syncthreads();
     // every piece needs a workgroup of the grid
@@ -549,7 +360,7 @@ __device__ Share plan_share(const AttnParams &p, int *lds) {
       const int cc = c < 0 ? 0 : c;
       int t = 0;
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) t += red[cc * kWaves + w];
+      for (int w = 0; w < NW; ++w) t += red[cc * NW + w];
       if (c >= 0 ? t * p.hkv <= one_per_cu : t * p.hkv <= (int)gridDim.x && cap == 0)
         cap = piece_cap(cc);
     }
@@ -568,7 +379,7 @@ __device__ Share plan_share(const AttnParams &p, int *lds) {
   const int lead = seg_mode ? 0 : kLeadKeys;
   int total_pc = 0, total_v = total, excl_pc = 0, excl_v = excl, sum_v = sum;
   if (seg_mode) {
-    excl_pc = block_excl_scan(npc, lds + kWaves, total_pc);
+    excl_pc = block_excl_scan<NW>(npc, lds + NW, total_pc);
   } else {
     int nnz = 0;  // this thread's segments with keys
     if (per == 1) {
@@ -577,7 +388,7 @@ __device__ Share plan_share(const AttnParams &p, int *lds) {
       for (int i = lo; i < hi; ++i) nnz += segment_len(p, i) > 0 ? 1 : 0;
     }
     sum_v = sum + lead * nnz;
-    excl_v = block_excl_scan(sum_v, lds + kWaves, total_v);
+    excl_v = block_excl_scan<NW>(sum_v, lds + NW, total_v);
     const int work_v = total_v * p.hkv;
     share = (work_v + (int)gridDim.x - 1) / (int)gridDim.x;
     share = max(kMinShare, round_up_block(share));
@@ -656,258 +467,523 @@ __device__ Share plan_share(const AttnParams &p, int *lds) {
     }
   }
   __syncthreads();
+  // Uniform by construction; declared so, or the compiler would treat every
+  // branch on the share as divergent.
+  auto uni = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+  const bool has = uni(seg_mode ? b < total_pc * p.hkv : start < work_s) != 0;
   Share sh;
-  sh.lead = lead;
-  const bool has = seg_mode ? b < total_pc * p.hkv : start < work_s;
-  if (has) {
-    sh.start = __builtin_amdgcn_readfirstlane(loc[6]);
-    sh.end = __builtin_amdgcn_readfirstlane(loc[7]);
-    sh.i = __builtin_amdgcn_readfirstlane(loc[0]);
-    sh.g = __builtin_amdgcn_readfirstlane(loc[1]);
-    sh.off = __builtin_amdgcn_readfirstlane(loc[2]);
-    const int f0 = __builtin_amdgcn_readfirstlane(loc[3]);
-    const int f1 = __builtin_amdgcn_readfirstlane(loc[4]);
-    sh.first.q0 = f0;
-    sh.first.ctx = __builtin_amdgcn_readfirstlane(loc[5]);
-    sh.first.k = f1 - f0;
-    sh.first.len = sh.first.ctx + sh.first.k;
-    sh.first.seg = segment_of(p, f0, f1, sh.first.ctx);
-  } else {
-    sh.start = sh.end = work_s;
-    sh.i = sh.g = sh.off = 0;
-    sh.first = ReqMeta{0, 0, 0, 0, 0};
-  }
+  sh.lead = uni(lead);
+  sh.start = has ? uni(loc[6]) : 0;
+  sh.end = has ? uni(loc[7]) : 0;
+  sh.i = uni(loc[0]);
+  sh.g = uni(loc[1]);
+  sh.off = uni(loc[2]);
+  const int f0 = uni(loc[3]), f1 = uni(loc[4]);
+  sh.first.q0 = f0;
+  sh.first.ctx = uni(loc[5]);
+  sh.first.k = f1 - f0;
+  sh.first.len = sh.first.ctx + sh.first.k;
+  sh.first.seg = segment_of(p, f0, f1, sh.first.ctx);
   return sh;
 }
 
-// Everything a wave needs to run the ring over one sub-piece.
-template <int D>
+// The wave's query operands, and the last key each lane's row may see (-1: a
+// row past the live ones).
+template <int D, int TW>
+struct QOps {
+  bf16x8 r[TW][D / 32];
+  int row_limit[TW];
+};
+
+// Tiles tile0 .. tile0+TW-1 of request rq.  A row past the live ones loads row
+// 0 of the request and is zeroed, so that no load sits behind a branch of its
+// own.
+template <int D, int TW>
+__device__ __forceinline__ void load_q(const AttnParams &p, int g, const ReqMeta &rq, int tile0,
+                                       int lane, QOps<D, TW> &qv) {
+  const int kq = lane >> 4, n = lane & 15;
+  const int lg = __builtin_ctz(p.group);
+  u32x4 x[TW][D / 32];
+#pragma unroll
+  for (int t = 0; t < TW; ++t) {
+    const int rr = (tile0 + t) * 16 + n;
+    const bool valid = rr < p.group * rq.k;
+    const int at = valid ? rr : 0;
+    const int j = at >> lg, hh = at & (p.group - 1);
+    qv.row_limit[t] = valid ? rq.ctx + j : -1;
+    const uint16_t *row = p.q + ((size_t)(rq.q0 + j) * p.hq + (size_t)g * p.group + hh) * D;
+#pragma unroll
+    for (int c = 0; c < D / 32; ++c)
+      x[t][c] = *reinterpret_cast<const u32x4 *>(row + 32 * c + 8 * kq);
+  }
+#pragma unroll
+  for (int t = 0; t < TW; ++t) {
+    const uint32_t keep = qv.row_limit[t] >= 0 ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+    for (int c = 0; c < D / 32; ++c)
+      qv.r[t][c] = as_bf16x8(__builtin_bit_cast(uint4, x[t][c] & u32x4{keep, keep, keep, keep}));
+  }
+}
+
+template <int TW, int NE>
+__device__ __forceinline__ void clear_state(RowState<TW, NE> &st) {
+#pragma unroll
+  for (int t = 0; t < TW; ++t) {
+    st.m[t] = kNoMax;
+    st.l[t] = 0.f;
+#pragma unroll
+    for (int u = 0; u < NE; ++u) st.o[t][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+}
+
+// Scores of one step for the wave's tiles (raw: the scale is positive and
+// applied inside the exponent).  Element (h, q) of a lane is key
+// t0 + 16h + 4*(lane>>4) + q.
+template <int D, int TW>
+struct Scores {
+  f32x4 x[TW][Step<D>::kPages];
+};
+template <int D, int TW>
+__device__ __forceinline__ void step_scores(const KRegs<D> &k, const QOps<D, TW> &qv,
+                                            Scores<D, TW> &s) {
+#pragma unroll
+  for (int t = 0; t < TW; ++t) {
+#pragma unroll
+    for (int h = 0; h < Step<D>::kPages; ++h) s.x[t][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < D / 32; ++c) {
+#pragma unroll
+      for (int h = 0; h < Step<D>::kPages; ++h)
+        s.x[t][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            as_bf16x8(__builtin_bit_cast(uint4, k.x[h][c])), qv.r[t][c], s.x[t][h], 0, 0, 0);
+    }
+  }
+}
+
+// Causal and end-of-request masking of a step that not every live row sees
+// whole.  Keys at or past `se` may hold anything (even NaN), so their V is
+// zeroed as well.
+template <int D, int TW, int NE>
+__device__ __forceinline__ void step_mask(int t0, int se, const int (&row_limit)[TW], int lane,
+                                          Scores<D, TW> &s, VRegs<D, NE> &v) {
+  const int kq = lane >> 4;
+#pragma unroll
+  for (int t = 0; t < TW; ++t)
+#pragma unroll
+    for (int h = 0; h < Step<D>::kPages; ++h)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int key = t0 + 16 * h + 4 * kq + q;
+        if (key > row_limit[t] || key >= se) s.x[t][h][q] = -INFINITY;
+      }
+#pragma unroll
+  for (int e = 0; e < Step<D>::kPairs; ++e) {
+    const int tb = t0 + 32 * e + 16 * (kq & 1) + 8 * (kq >> 1);
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const uint32_t mask = (tb + 2 * w < se ? 0x0000FFFFu : 0u) |
+                            (tb + 2 * w + 1 < se ? 0xFFFF0000u : 0u);
+#pragma unroll
+      for (int u = 0; u < NE; ++u) v.x[e][u][w] &= mask;
+    }
+  }
+}
+
+// Online softmax and the PV product of one step.
+template <int D, int TW, int NE>
+__device__ __forceinline__ void step_update(const Scores<D, TW> &s, const VRegs<D, NE> &v,
+                                            float scale_log2, RowState<TW, NE> &st) {
+  constexpr int kPages = Step<D>::kPages;
+  // a lane's own keys decide whether any row's maximum moves; only then are
+  // the row's four lanes brought together
+  bool jump = false;
+#pragma unroll
+  for (int t = 0; t < TW; ++t) {
+    float top = -INFINITY;
+#pragma unroll
+    for (int h = 0; h < kPages; ++h)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        top = fmaxf(top, __builtin_fmaf(s.x[t][h][q], scale_log2, -st.m[t]));
+    jump |= top > kRescaleSlack;
+  }
+  if (__builtin_amdgcn_ballot_w64(jump) != 0) {
+#pragma unroll
+    for (int t = 0; t < TW; ++t) {
+      float top = -INFINITY;
+#pragma unroll
+      for (int h = 0; h < kPages; ++h)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) top = fmaxf(top, s.x[t][h][q]);
+      const float m_new = fmaxf(st.m[t], ceilf(row_max4(top) * scale_log2));
+      // 0 on a row's first visible step, 1 for a row that still sees nothing
+      const float alpha = __builtin_amdgcn_exp2f(st.m[t] - m_new);
+      st.l[t] *= alpha;
+#pragma unroll
+      for (int u = 0; u < NE; ++u) st.o[t][u] *= alpha;
+      st.m[t] = m_new;
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < TW; ++t) {
+#pragma unroll
+    for (int e = 0; e < Step<D>::kPairs; ++e) {
+      // P enters the bf16 PV product as a pair: hi = P rounded to bf16 and
+      // lo = the remainder rounded to bf16, so hi + lo carries P to about
+      // 2^-17 of its value and the weights add no error next to the output's
+      // own bf16 rounding.  The row sum adds the fp32 weights themselves.
+      uint32_t hi[2][2], lo[2][2];
+      float psum[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        float pw[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          pw[q] = __builtin_amdgcn_exp2f(
+              __builtin_fmaf(s.x[t][2 * e + h][q], scale_log2, -st.m[t]));
+        psum[h] = (pw[0] + pw[1]) + (pw[2] + pw[3]);
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+          const uint32_t x = pack_bf16x2(pw[2 * w], pw[2 * w + 1]);
+          hi[h][w] = x;
+          lo[h][w] = pack_bf16x2(pw[2 * w] - __uint_as_float(x << 16),
+                                 pw[2 * w + 1] - __uint_as_float(x & 0xFFFF0000u));
+        }
+      }
+      st.l[t] += psum[0] + psum[1];
+      // lane (kq, n) holds slots 4kq .. +3 of both pages; trading odd rows of
+      // page 0's against even rows of page 1's leaves it slots 8*(kq>>1) .. +7
+      // of page kq & 1, the keys of its V operand
+      const auto h0 = __builtin_amdgcn_permlane16_swap(hi[0][0], hi[1][0], false, false);
+      const auto h1 = __builtin_amdgcn_permlane16_swap(hi[0][1], hi[1][1], false, false);
+      const auto l0 = __builtin_amdgcn_permlane16_swap(lo[0][0], lo[1][0], false, false);
+      const auto l1 = __builtin_amdgcn_permlane16_swap(lo[0][1], lo[1][1], false, false);
+      const bf16x8 ph = as_bf16x8(make_uint4(h0[0], h1[0], h0[1], h1[1]));
+      const bf16x8 pl = as_bf16x8(make_uint4(l0[0], l1[0], l0[1], l1[1]));
+#pragma unroll
+      for (int u = 0; u < NE; ++u)
+        st.o[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            as_bf16x8(__builtin_bit_cast(uint4, v.x[e][u])), ph, st.o[t][u], 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < NE; ++u)
+        st.o[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            as_bf16x8(__builtin_bit_cast(uint4, v.x[e][u])), pl, st.o[t][u], 0, 0, 0);
+    }
+  }
+}
+
+// --------------------------------------------------------------------- ring
+// K and V stream through an LDS ring of kStages stages, all of them in flight
+// in registers: one step a stage with four waves, two with eight (a tile or
+// more for every wave).  Each wave loads its tiles of a stage (a page's K or
+// V, contiguous 1 KiB loads), writes them to the ring when the stage comes up,
+// and after the barrier the waves read their operands from it.  With four
+// waves, stages of two steps (two in flight, 128 KiB to a CU instead of 96)
+// measured slower: B=32, contexts to 8K 104.4 -> 107-112 us, with eight query
+// heads to a KV head and contexts to 16K 229 -> 238 us.
+template <int D, int NW>
+struct Ring {
+  static constexpr int kSteps = NW / 4;
+  static constexpr int kKeys = kSteps * Step<D>::kKeys;
+  static constexpr int kPages = kKeys / kPage;
+  static constexpr int kTile = kPage * D * 2;          // bytes of a page's K or V
+  static constexpr int kStage = 2 * kPages * kTile;    // K tiles, then V tiles (kSteps * 16 KiB)
+  static constexpr int kStages = 3;
+  static constexpr int kTiles = 2 * kPages / NW;       // tiles a wave loads per stage
+  static constexpr int kBytes = kStages * kStage;
+  // page and kind (0: K, 1: V) of a wave's q-th tile
+  static __device__ __forceinline__ int page(int wave, int q) { return (wave * kTiles + q) >> 1; }
+  static __device__ __forceinline__ int kind(int wave, int q) { return (wave * kTiles + q) & 1; }
+};
+
+// V tiles sit in the ring with their 16-byte units (dim, half of the slots)
+// permuted inside each 1 KiB, so that the operand reads are free of bank
+// conflicts: global unit u = 2*dim + half is LDS unit v_unit(u), and
+// v_unit_inv is the inverse.  Aligned groups of four lanes still load aligned
+// 64-byte pieces.
+__device__ __forceinline__ int v_sel(int k) { return ((k >> 1) ^ (k >> 2)) & 1; }
+__device__ __forceinline__ int v_unit(int u) {
+  const int k = u >> 2, j = (u >> 1) & 1, b = u & 1;
+  return 4 * k + 2 * (b ^ v_sel(k)) + j;
+}
+__device__ __forceinline__ int v_unit_inv(int l) {
+  const int k = l >> 2, j = l & 1, b = ((l >> 1) & 1) ^ v_sel(k);
+  return 4 * k + 2 * j + b;
+}
+
+// What a wave needs to run the ring over one sub-piece.
 struct RingCtx {
-  const char *ring;      // LDS ring base
-  const int *pg;         // LDS page ids of the sub-piece (sanitised)
-  const char *kvw;       // this wave's tile of page 0: kv + (kind*Hkv + g) tiles
-  size_t page_bytes;     // bytes per page (2 * Hkv tiles)
-  uint32_t dst0;         // byte offset of this wave's tile region in a stage
-  uint32_t voff;         // this lane's swizzled global offset inside a chunk
-  int pp;                // page parity this wave loads
-  RingLane rl;
-  uint32_t vb;           // V operand offset of the wave's first d block
-  int nblk;              // blocks in the sub-piece
-  int sb, se, ctx, row_limit;
-  int prio_end_b;        // block at which the wave priority returns to the default
+  const int *ids;        // LDS: page ids of the sub-piece
+  const char *kbase;     // K tile of page 0, this KV head, plus the lane's offset
+  const char *vbase;     // V tile of page 0, this KV head, plus the lane's offset
+  uint32_t page_bytes;   // bytes per page (2 * Hkv tiles)
+  int ns;                // stages
+  int sb, se, ctx;       // first key, end of the keys, committed context
+  int prio_end;          // key at which the wave priority returns to the default
+};
+
+template <int D, int NW>
+struct StageRegs {
+  u32x4 x[Ring<D, NW>::kTiles][D / 32];
+};
+
+// Loads the wave's tiles of stage b.  Past the last stage it reads page 0
+// instead (in cache, never used): the loop then has one shape, and the
+// compiler can wait for exactly the stage each step writes.
+template <int D, int NW>
+__device__ __forceinline__ void ring_load(const RingCtx &c, int b, int wave,
+                                          StageRegs<D, NW> &r) {
+  using R = Ring<D, NW>;
+#pragma unroll
+  for (int q = 0; q < R::kTiles; ++q) {
+    const int at = R::kPages * min(b, c.ns - 1) + R::page(wave, q);
+    const int id = b < c.ns ? __builtin_amdgcn_readfirstlane(c.ids[at]) : 0;
+    const char *t =
+        (R::kind(wave, q) ? c.vbase : c.kbase) + (size_t)(uint32_t)id * c.page_bytes;
+#pragma unroll
+    for (int x = 0; x < D / 32; ++x)
+      r.x[q][x] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(t + 1024 * x));
+  }
+}
+
+// A wave's part of the work on a piece: its row tiles and its d blocks.
+struct Role {
+  int tile0, e_lo;
   bool active;
 };
 
-// Address of this wave's tile of block b (clamped: past the end it reloads
-// the last block, which is never read).
-template <int D>
-__device__ __forceinline__ const char *tile_of(const RingCtx<D> &c, int b) {
-  const int bb = min(b, c.nblk - 1);
-  const int pid = __builtin_amdgcn_readfirstlane(c.pg[2 * bb + c.pp]);
-  return c.kvw + (size_t)pid * c.page_bytes;
-}
-
-// One pipeline step with block b in compile-time stage ST: write the wave's
-// tile of block b (in registers since three steps ago) to the stage, start
-// loading block b + kStages into those registers, and after the barrier
-// compute block b.  The stage was last read at step b - kStages, which every
-// wave finished before the barrier of step b - kStages + 1.
-template <int D, int NE, int ST>
-__device__ __forceinline__ void ring_step(const RingCtx<D> &c, char *ring, int b,
-                                          StageRegs<D> &regs, const bf16x8 (&qv)[D / 32],
-                                          float scale_log2, int lane, RowState<D> &st) {
-  using R = Ring<D>;
-  stage_store<D>(ring + ST * R::kStage + c.dst0, lane, regs);
-  stage_load<D>(tile_of<D>(c, b + kStages), c.voff, regs);
+// One stage in ring slot S: write it, load the stage kStages ahead, and after
+// the barrier compute the wave's steps of it.
+template <int D, int TW, int NE, int NW, int S>
+__device__ __forceinline__ void ring_step(const RingCtx &c, char *ring, int b, int wave, int lane,
+                                          StageRegs<D, NW> &r, const QOps<D, TW> &qv,
+                                          const Role &role, float scale_log2,
+                                          RowState<TW, NE> &st) {
+  using R = Ring<D, NW>;
+  char *stage = ring + S * R::kStage;
+#pragma unroll
+  for (int q = 0; q < R::kTiles; ++q) {
+    char *dst = stage + (R::kind(wave, q) * R::kPages + R::page(wave, q)) * R::kTile + 16 * lane;
+#pragma unroll
+    for (int x = 0; x < D / 32; ++x) *reinterpret_cast<u32x4 *>(dst + 1024 * x) = r.x[q][x];
+  }
+  ring_load<D, NW>(c, b + R::kStages, wave, r);
   __syncthreads();
-  if (b == c.prio_end_b) __builtin_amdgcn_s_setprio(0);
-  if (c.active) {
-    const int t0 = c.sb + b * kBlockKeys;
-    const bool full = t0 + kBlockKeys <= min(c.ctx, c.se);
-    ring_compute<D, NE>(c.ring, ST * R::kStage, c.rl, c.vb, lane, t0, c.se, c.row_limit, full,
-                        qv, scale_log2, st);
+  if (c.sb + b * R::kKeys >= c.prio_end) __builtin_amdgcn_s_setprio(0);
+  if (!role.active) return;
+  const int kq = lane >> 4, m = lane & 15;
+  const char *vb = stage + (R::kPages + (kq & 1)) * R::kTile + 16 * v_unit(2 * m + (kq >> 1)) +
+                   512 * role.e_lo;
+#pragma unroll 1
+  for (int sub = 0; sub < R::kSteps; ++sub) {
+    const int t0 = c.sb + b * R::kKeys + sub * Step<D>::kKeys;
+    if (t0 >= c.se) break;
+    KRegs<D> k;
+#pragma unroll
+    for (int h = 0; h < Step<D>::kPages; ++h)
+#pragma unroll
+      for (int x = 0; x < D / 32; ++x)
+        k.x[h][x] = *reinterpret_cast<const u32x4 *>(
+            stage + (sub * Step<D>::kPages + h) * R::kTile + 1024 * x + 16 * lane);
+    Scores<D, TW> s;
+    step_scores<D, TW>(k, qv, s);
+    // V's reads stay behind the score products: their registers are K's
+    __builtin_amdgcn_sched_barrier(0);
+    VRegs<D, NE> v;
+#pragma unroll
+    for (int e = 0; e < Step<D>::kPairs; ++e)
+#pragma unroll
+      for (int u = 0; u < NE; ++u)
+        v.x[e][u] = *reinterpret_cast<const u32x4 *>(
+            vb + (sub * Step<D>::kPages + 2 * e) * R::kTile + 512 * u);
+    if (t0 + Step<D>::kKeys > min(c.ctx, c.se))
+      step_mask<D, TW, NE>(t0, c.se, qv.row_limit, lane, s, v);
+    step_update<D, TW, NE>(s, v, scale_log2, st);
   }
 }
 
-// Steps S .. kStages-1 of one round of the block loop (one step per ring
-// stage, the stage index a compile-time constant); true once the sub-piece's
-// last block has been computed.
-template <int D, int NE, int S>
-struct RingRound {
-  static __device__ __forceinline__ bool run(const RingCtx<D> &c, char *ring, int b,
-                                             StageRegs<D> (&r)[kStages],
-                                             const bf16x8 (&qv)[D / 32], float scale_log2,
-                                             int lane, RowState<D> &st) {
-    ring_step<D, NE, S>(c, ring, b + S, r[S], qv, scale_log2, lane, st);
-    if (b + S + 1 >= c.nblk) return true;
-    return RingRound<D, NE, S + 1>::run(c, ring, b, r, qv, scale_log2, lane, st);
-  }
-};
-template <int D, int NE>
-struct RingRound<D, NE, kStages> {
-  static __device__ __forceinline__ bool run(const RingCtx<D> &, char *, int,
-                                             StageRegs<D> (&)[kStages],
-                                             const bf16x8 (&)[D / 32], float, int,
-                                             RowState<D> &) {
-    return false;
-  }
-};
-
-// All blocks of one sub-piece through the ring.
-template <int D, int NE>
-__device__ __forceinline__ void ring_run(const RingCtx<D> &c, char *ring,
-                                         const bf16x8 (&qv)[D / 32], float scale_log2, int lane,
-                                         RowState<D> &st) {
-  // issued in block order (the empty asm keeps the compiler from reordering
-  // them), so that each step waits only for its own block
-  StageRegs<D> r[kStages];
+// All stages of one sub-piece.
+template <int D, int TW, int NE, int NW>
+__device__ __forceinline__ void ring_run(const RingCtx &c, char *ring, int wave, int lane,
+                                         const QOps<D, TW> &qv, const Role &role,
+                                         float scale_log2, RowState<TW, NE> &st) {
+  constexpr int kStages = Ring<D, NW>::kStages;
+  StageRegs<D, NW> r[kStages];
+  // issued in stage order (the empty asm keeps the compiler from reordering
+  // them), so that each step waits only for its own stage
 #pragma unroll
   for (int s = 0; s < kStages; ++s) {
-    stage_load<D>(tile_of<D>(c, s), c.voff, r[s]);
+    ring_load<D, NW>(c, s, wave, r[s]);
     asm volatile("" ::: "memory");
   }
-  // the loop leaves only when a round reports the last block, so every path
-  // back to its head has issued the same loads in the same order and the
-  // compiler can wait for exactly the block each step writes
-  for (int b = 0;; b += kStages)
-    if (RingRound<D, NE, 0>::run(c, ring, b, r, qv, scale_log2, lane, st)) break;
-  __syncthreads();  // the ring is free for the next sub-piece
+  for (int b = 0; b < c.ns; b += kStages) {
+    ring_step<D, TW, NE, NW, 0>(c, ring, b, wave, lane, r[0], qv, role, scale_log2, st);
+    ring_step<D, TW, NE, NW, 1>(c, ring, b + 1, wave, lane, r[1], qv, role, scale_log2,
+                                        st);
+    ring_step<D, TW, NE, NW, 2>(c, ring, b + 2, wave, lane, r[2], qv, role, scale_log2, st);
+  }
 }
 
-template <int D>
-__global__ __launch_bounds__(kThreads, 2) void attn_streamk_kernel(AttnParams p) {
-  using R = Ring<D>;
-  __shared__ __attribute__((aligned(1024))) char ring[kStages * R::kStage];
-  __shared__ int pg[kSubPages + 8];
-  __shared__ int lds_plan[2 * kWaves + 8 + kNumPieceCaps * kWaves];
+// ------------------------------------------------------------------- pieces
+// A piece: the workgroup's keys [key_begin, key_end) of request i, KV head g.
+struct Piece {
+  int i, g, key_begin, key_end, slot, prio_end;
+  bool complete;
+  ReqMeta rq;
+};
 
-  const Share sh = plan_share(p, lds_plan);
+// Writes NE d blocks from e_lo of a finished row tile: bf16 output when the
+// piece is the whole segment, otherwise the fp32 partial in this workgroup's
+// slot (0: the segment where its share starts, 1: where it ends), with (m, l)
+// beside d block 0.
+template <int D, int NE>
+__device__ __forceinline__ void write_rows(const AttnParams &p, const Piece &x, int rt, int e_lo,
+                                           int lane, float m, float l, const f32x4 (&o)[NE]) {
+  const int kq = lane >> 4;
+  const int rr = rt * 16 + (lane & 15);
+  if (rr >= p.group * x.rq.k) return;
+  const int dim = 16 * e_lo + 4 * kq;
+  if (x.complete) {
+    const int lg = __builtin_ctz(p.group);
+    const int j = rr >> lg, hh = rr & (p.group - 1);
+    const size_t row = (size_t)(x.rq.q0 + j) * p.hq + (size_t)x.g * p.group + hh;
+    const float inv = 1.f / l;
+#pragma unroll
+    for (int u = 0; u < NE; ++u) {
+      uint2 w;
+      w.x = pack_bf16x2(o[u][0] * inv, o[u][1] * inv);
+      w.y = pack_bf16x2(o[u][2] * inv, o[u][3] * inv);
+      *reinterpret_cast<uint2 *>(p.out + row * D + dim + 16 * u) = w;
+    }
+  } else {
+    const size_t prow = ((size_t)blockIdx.x * 2 + x.slot) * (p.group * kMaxQlen) + rr;
+#pragma unroll
+    for (int u = 0; u < NE; ++u)
+      *reinterpret_cast<f32x4 *>(p.part_o + prow * D + dim + 16 * u) = o[u];
+    if (e_lo == 0 && kq == 0) p.part_ml[prow] = make_float2(m, l);
+  }
+}
+
+// Wave roles.  NE < D/16 d blocks: the waves split one tile's dims (or two
+// tiles', half of the waves each).  All of them: each wave has TW tiles to
+// itself.
+template <int D, int TW, int NE, int NW>
+__device__ __forceinline__ void run_piece(const AttnParams &p, char *buf, int *ids, const Piece &x,
+                                          int wave, int lane) {
+  using R = Ring<D, NW>;
+  constexpr int kParts = D / 16 / NE;  // waves to a tile
+  Role role;
+  role.tile0 = wave / kParts * TW;
+  role.e_lo = wave % kParts * NE;
+  role.active = role.tile0 * 16 < p.group * x.rq.k;
+  RowState<TW, NE> st;
+  QOps<D, TW> qv;
+  load_q<D, TW>(p, x.g, x.rq, role.tile0, lane, qv);
+  clear_state<TW, NE>(st);
+  RingCtx c;
+  c.ids = ids;
+  c.page_bytes = (uint32_t)(2 * p.hkv * kPage * D * (int)sizeof(uint16_t));
+  c.kbase = reinterpret_cast<const char *>(p.kv) + (size_t)x.g * kPage * D * sizeof(uint16_t) +
+            16 * lane;
+  c.vbase = reinterpret_cast<const char *>(p.kv) +
+            (size_t)(p.hkv + x.g) * kPage * D * sizeof(uint16_t) + 16 * v_unit_inv(lane);
+  c.ctx = x.rq.ctx;
+  c.prio_end = x.prio_end;
+  for (int sb = x.key_begin; sb < x.key_end; sb += kSubKeys) {
+    const int se = min(x.key_end, sb + kSubKeys);
+    c.sb = sb;
+    c.se = se;
+    c.ns = (se - sb + R::kKeys - 1) / R::kKeys;
+    // the sub-piece's page ids; an id outside [0, num_pages) breaks the
+    // contract and reads page 0 instead (valid memory, result unspecified),
+    // pages past the sub-piece read page 0 and are masked
+    const int npg = (se - sb + kPage - 1) / kPage;
+    const int *pt = p.page_table + (size_t)x.i * p.max_pages + sb / kPage;
+    if (sb > x.key_begin) __syncthreads();  // the last ids and stages have been read
+    for (int t = threadIdx.x; t < R::kPages * c.ns; t += NW * kWave) {
+      const int id = t < npg ? pt[t] : 0;
+      ids[t] = (unsigned)id < (unsigned)p.num_pages ? id : 0;
+    }
+    __syncthreads();
+    ring_run<D, TW, NE, NW>(c, buf, wave, lane, qv, role, p.scale_log2, st);
+  }
+  if (!role.active) return;
+#pragma unroll
+  for (int t = 0; t < TW; ++t)
+    write_rows<D, NE>(p, x, role.tile0 + t, role.e_lo, lane, st.m[t], row_sum4(st.l[t]), st.o[t]);
+}
+
+// NW waves: four, two workgroups to a CU; eight, one to a CU, for G = 16,
+// whose requests may have more than eight row tiles.
+template <int D, int NW>
+__global__ __launch_bounds__(NW *kWave, 2) void attn_streamk_kernel(AttnParams p) {
+  __shared__ __attribute__((aligned(1024))) char buf[Ring<D, NW>::kBytes];
+  __shared__ int ids[kSubPages];
+  __shared__ int lds_plan[2 * NW + 8 + kNumPieceCaps * NW];
+
+  const Share sh = plan_share<NW>(p, lds_plan);
   if (sh.start >= sh.end) return;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int lane = threadIdx.x % kWave;
-  const int kq = lane >> 4, n = lane & 15;
+  int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  int lane = threadIdx.x % kWave;
+
   // keys of the share (virtual) run at raised priority; -1: none
   const bool boost = (int)blockIdx.x >= p.num_cu;
   if (boost) __builtin_amdgcn_s_setprio(1);
-  const int boost_keys = boost ? (int)((long long)(sh.end - sh.start) * kBoostPct / 100) : -1;
+  const int boost_end = boost ? sh.start + (int)((long long)(sh.end - sh.start) * kBoostPct / 100) : -1;
 
-  // this wave's share of every ring load: page parity pp, K (waves 0-1) or V
-  const int pp = wave & 1, kind = wave >> 1;
-  RingCtx<D> c;
-  c.ring = ring;
-  c.pg = pg;
-  c.pp = pp;
-  c.page_bytes = (size_t)2 * p.hkv * kPage * D * sizeof(uint16_t);
-  c.dst0 = kind * R::kKRegion + pp * R::kChunks * 1024;
-  c.voff = 16u * (uint32_t)(kind == 0 ? k_unit(lane, pp) : v_unit_inv(lane));
-  c.rl = ring_lane<D>(lane);
-
-  int i = sh.i, g = sh.g, off = sh.off, pos = sh.start, piece = 0;
+  Piece x;
+  x.i = sh.i;
+  x.g = sh.g;
+  x.rq = sh.first;
+  int off = sh.off, pos = sh.start, piece = 0;
   // metadata of the request last read: the next KV head's segment of the
   // same request (the usual next piece) needs no second read of it
   int i_meta = sh.i;
-  ReqMeta meta = sh.first;
-  while (pos < sh.end && i < p.num_reqs) {
-    if (i != i_meta) {
-      meta = load_req(p, i);
-      i_meta = i;
+  while (pos < sh.end && x.i < p.num_reqs) {
+    if (x.i != i_meta) {
+      x.rq = load_req(p, x.i);
+      i_meta = x.i;
     }
-    const ReqMeta rq = meta;
-    if (rq.seg == 0) {  // sentinel or bad metadata: no keys in the plan
-      ++i;
+    if (x.rq.seg == 0) {  // sentinel or bad metadata: no keys in the plan
+      ++x.i;
       continue;
     }
     // offsets are virtual: the segment's keys follow its lead-in of
     // sh.lead keys (none in the small-batch plan)
-    const int segv = rq.seg + sh.lead;
+    const int segv = x.rq.seg + sh.lead;
     const int take = min(segv - off, sh.end - pos);
-    const int key_begin = max(off - sh.lead, 0);
-    const int key_end = min(rq.len, off + take - sh.lead);
-    if (key_end <= key_begin) break;  // the share ends inside the lead-in
-    const bool complete = off <= sh.lead && off + take == segv;
-    const int slot = piece == 0 ? 0 : 1;
-    c.kvw = reinterpret_cast<const char *>(p.kv) +
-            (size_t)(kind * p.hkv + g) * kPage * D * sizeof(uint16_t);
-    c.ctx = rq.ctx;
+    x.key_begin = max(off - sh.lead, 0);
+    x.key_end = min(x.rq.len, off + take - sh.lead);
+    if (x.key_end <= x.key_begin) break;  // the share ends inside the lead-in
+    x.complete = off <= sh.lead && off + take == segv;
+    x.slot = piece == 0 ? 0 : 1;
+    x.prio_end = boost ? x.key_begin + boost_end - pos : 0x7FFFFFFF;
+    if (piece > 0) __syncthreads();  // the last piece's LDS has been read
 
-    // Wave roles.  Every wave computes every block of the piece:
-    //  1 row tile:  all four waves on it, each with a quarter of the dims;
-    //  2 row tiles: two waves per tile, each with half of the dims;
-    //  3+ tiles:    one tile per wave, all dims (passes of four tiles).
-    const int rows = p.group * rq.k;
-    const int nt = (rows + 15) / 16;
-    const int nds = nt == 1 ? 4 : (nt == 2 ? 2 : 1);
-    const int npass = (nt + kWaves - 1) / kWaves;
-    const int ne = (D / 16) / nds;
-    for (int pass = 0; pass < npass; ++pass) {
-      const int rt = nds > 1 ? wave % nt : wave + kWaves * pass;
-      const int ds = nds > 1 ? wave / nt : 0;
-      c.active = rt < nt;
-      const int e_lo = ds * ne;
-      c.vb = c.rl.v + 512u * (uint32_t)e_lo;
-      const int rr = rt * 16 + n;
-      const bool valid_row = c.active && rr < rows;
-      const int lg = __builtin_ctz(p.group);
-      const int j = rr >> lg, hh = rr & (p.group - 1);
-      c.row_limit = valid_row ? rq.ctx + j : -1;
-      bf16x8 qv[D / 32];
-      {
-        const uint16_t *qrow =
-            p.q + ((size_t)(rq.q0 + j) * p.hq + (size_t)g * p.group + hh) * D;
-#pragma unroll
-        for (int cc = 0; cc < D / 32; ++cc) {
-          uint4 x = make_uint4(0, 0, 0, 0);
-          if (valid_row) x = *reinterpret_cast<const uint4 *>(qrow + 32 * cc + 8 * kq);
-          qv[cc] = as_bf16x8(x);
-        }
-
-      }
-      RowState<D> st;
-      st.m = -INFINITY;
-      st.l = 0.f;
-#pragma unroll
-      for (int e = 0; e < D / 16; ++e) st.o[e] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-      for (int sb = key_begin; sb < key_end; sb += kSubPages * kPage) {
-        const int se = min(key_end, sb + kSubPages * kPage);
-        c.sb = sb;
-        c.se = se;
-        c.nblk = (se - sb + kBlockKeys - 1) / kBlockKeys;
-        c.prio_end_b = -1;
-        if (boost_keys >= 0) {
-          const int left = boost_keys - ((pos - sh.start) + (sb - key_begin));
-          c.prio_end_b = left <= 0 ? 0 : (left + kBlockKeys - 1) / kBlockKeys;
-        }
-        // stage the sub-piece's page ids; an id outside [0, num_pages) breaks
-        // the contract and reads page 0 instead (valid memory, result
-        // unspecified), pages past the sub-piece read page 0 and are masked
-        {
-          const int npg = (se - sb + kPage - 1) / kPage;
-          const int *pt = p.page_table + (size_t)i * p.max_pages + sb / kPage;
-          for (int t = threadIdx.x; t < 2 * c.nblk; t += kThreads) {
-            int id = t < npg ? pt[t] : 0;
-            pg[t] = (unsigned)id < (unsigned)p.num_pages ? id : 0;
-          }
-          __syncthreads();
-        }
-        if (ne == D / 16)
-          ring_run<D, D / 16>(c, ring, qv, p.scale_log2, lane, st);
-        else if (ne == D / 32)
-          ring_run<D, D / 32>(c, ring, qv, p.scale_log2, lane, st);
-        else
-          ring_run<D, D / 64>(c, ring, qv, p.scale_log2, lane, st);
-      }
-      if (c.active) write_tile<D>(p, g, complete, slot, rq, rt, e_lo, ne, lane, st.l, st);
-    }
+    // opaque per piece: or the compiler computes every lane's offsets for all
+    // the piece forms ahead of the loop, and spills them
+    asm volatile("" : "+v"(lane), "+s"(wave));
+    const int nt = (p.group * x.rq.k + 15) / 16;  // row tiles
+    // one or two tiles split their dims over the waves (with eight waves, which
+    // serve G = 16, so short a request leaves the others idle)
+    constexpr int kBlocks = D / 16;
+    if (NW == 4 && nt == 1)
+      run_piece<D, 1, kBlocks / 4, NW>(p, buf, ids, x, wave, lane);
+    else if (NW == 4 && nt == 2)
+      run_piece<D, 1, kBlocks / 2, NW>(p, buf, ids, x, wave, lane);
+    else if (nt <= NW)
+      run_piece<D, 1, kBlocks, NW>(p, buf, ids, x, wave, lane);
+    else
+      run_piece<D, 2, kBlocks, NW>(p, buf, ids, x, wave, lane);
 
     pos += take;
     off += take;
     ++piece;
     if (off == segv) {
       off = 0;
-      if (++g == p.hkv) {
-        g = 0;
-        ++i;
+      if (++x.g == p.hkv) {
+        x.g = 0;
+        ++x.i;
       }
     }
   }
@@ -1057,21 +1133,30 @@ int device_cus() {
   return cus;
 }
 
-// Workgroups the GPU holds at once for the stream-K kernel (cached per
-// device and head dim; a host query, so it is safe during graph capture).
-int resident_workgroups(int head_dim) {
-  static int cache[64][2];
+// The split kernel for a head dim and GQA group, and its threads.
+struct SplitKernel {
+  void (*fn)(AttnParams);
+  int threads;
+};
+SplitKernel split_kernel(int head_dim, int group) {
+  if (group > 8)
+    return {head_dim == 128 ? attn_streamk_kernel<128, 8> : attn_streamk_kernel<64, 8>, 8 * kWave};
+  return {head_dim == 128 ? attn_streamk_kernel<128, 4> : attn_streamk_kernel<64, 4>, 4 * kWave};
+}
+
+// Workgroups the GPU holds at once for the split kernel (cached per device
+// and kernel; a host query, so it is safe during graph capture).
+int resident_workgroups(int head_dim, int group) {
+  static int cache[64][4];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
-  int &slot = cache[dev][head_dim == 128 ? 1 : 0];
+  int &slot = cache[dev][(head_dim == 128 ? 1 : 0) + (group > 8 ? 2 : 0)];
   if (slot > 0) return slot;
-  int cus = 0, per_cu = 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    return 0;
-  const hipError_t e =
-      head_dim == 128
-          ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_streamk_kernel<128>, kThreads, 0)
-          : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, attn_streamk_kernel<64>, kThreads, 0);
+  const int cus = device_cus();
+  int per_cu = 0;
+  const SplitKernel k = split_kernel(head_dim, group);
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+      &per_cu, reinterpret_cast<const void *>(k.fn), k.threads, 0);
   if (e != hipSuccess || cus <= 0 || per_cu <= 0) return 0;
   slot = cus * per_cu;
   return slot;
@@ -1094,7 +1179,7 @@ int32_t attn_num_cu() { return device_cus(); }
 
 // Launch grid: the workgroups the current device holds at once, capped.
 int32_t attn_grid(const dsv_attn_dims &d) {
-  const int r = resident_workgroups(d.head_dim);
+  const int r = resident_workgroups(d.head_dim, d.num_q_heads / d.num_kv_heads);
   if (r <= 0) return 0;
   const int32_t cap = attn_grid_cap(d);
   return r < cap ? r : cap;
@@ -1118,10 +1203,8 @@ hipError_t launch_verify_attn(const AttnParams &p, int head_dim, hipStream_t s) 
   const dim3 grid_comb((p.group * kMaxQlen + comb_rows - 1) / comb_rows, p.hkv,
                        p.num_reqs + 1);
   timing_mark(kTimeAttnSplit, false, s);
-  if (head_dim == 128)
-    hipLaunchKernelGGL(attn_streamk_kernel<128>, dim3(p.num_wg), dim3(kThreads), 0, s, p);
-  else
-    hipLaunchKernelGGL(attn_streamk_kernel<64>, dim3(p.num_wg), dim3(kThreads), 0, s, p);
+  const SplitKernel split = split_kernel(head_dim, p.group);
+  hipLaunchKernelGGL(split.fn, dim3(p.num_wg), dim3(split.threads), 0, s, p);
   timing_mark(kTimeAttnSplit, true, s);
   timing_mark(kTimeAttnCombine, false, s);
   if (head_dim == 128)
