@@ -64,8 +64,8 @@
 //     units (16 tiles to a key), then 33 MB of partials; 104 -> 62
 //   B=32, head_dim 64, contexts to 8K (0.3 GB): HBM; 60.7 -> 59.0
 //   B=8, full blocks, contexts to 2K (40 MB): the chain from launch to the
-//     last block; 23.4 -> 22.0
-//   B=1, full block, context 700 (3 MB): the same; 16.9 -> 15.9
+//     last block; 23.4 -> 22.1
+//   B=1, full block, context 700 (3 MB): the same; 16.9 -> 14.4
 #include "dsv_internal.h"
 
 #include <math.h>
@@ -230,13 +230,18 @@ struct Share {
 // instead cut into pieces of at most `cap` keys, as equal as whole blocks
 // allow, one piece per workgroup: no workgroup then pays for a second piece
 // (its metadata, page ids and pipeline refill), which at this size is a
-// large part of the kernel.  The cap is the smallest of kPieceCaps blocks
-// that leaves at most one piece per CU -- a second workgroup on a CU shares
-// its MFMA and LDS with the first and finishes last -- else the smallest,
-// if the pieces fit the grid.  Piece q of n of a `seg`-key segment starts at
+// large part of the kernel.  The cap leaves at most one piece per CU -- a
+// second workgroup on a CU shares its MFMA and LDS with the first and finishes
+// last.  The smallest batches take the smallest cap from two blocks up that
+// does so with at most kMaxMerge pieces to a segment, which the combine kernel
+// loads in one round trip (one request, 716 keys, four layers: 63.1 -> 58.3 us
+// with three blocks instead of eight; 16 pieces to a segment took 70.6 us);
+// the others the smallest of 8 to 12 blocks that fits, else eight, if the
+// pieces fit the grid.  Piece q of n of a `seg`-key segment starts at
 // piece_begin(seg, n, q).
 constexpr int kNumPieceCaps = 5;
 __device__ __forceinline__ int piece_cap(int c) { return (8 + c) * kBlockKeys; }  // 8..12 blocks
+constexpr int kMaxMerge = 8;
 __device__ __forceinline__ int seg_pieces(int seg, int cap) { return (seg + cap - 1) / cap; }
 __device__ __forceinline__ int piece_begin(int seg, int n, int q) {
   return (int)((long long)(seg / kBlockKeys) * q / n) * kBlockKeys;
@@ -277,6 +282,17 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
   v += dpp_src<0x118, 0xf>(v);  // row_shr:8
   v += dpp_src<0x142, 0xa>(v);  // row_bcast:15
   v += dpp_src<0x143, 0xc>(v);  // row_bcast:31
+  return v;
+}
+
+// Largest of the wave's values (not negative), in lane 63.
+__device__ __forceinline__ int wave_max(int v) {
+  v = max(v, dpp_src<0x111, 0xf>(v));
+  v = max(v, dpp_src<0x112, 0xf>(v));
+  v = max(v, dpp_src<0x114, 0xf>(v));
+  v = max(v, dpp_src<0x118, 0xf>(v));
+  v = max(v, dpp_src<0x142, 0xa>(v));
+  v = max(v, dpp_src<0x143, 0xc>(v));
   return v;
 }
 
@@ -336,33 +352,55 @@ __device__ Share plan_share(const AttnParams &p, int *lds) {
   // barrier) and pick the cap; every workgroup computes the same choice.
   int cap = 0;
   if (share == kMinShare) {
-    int cnt[kNumPieceCaps];
-#pragma unroll
-    for (int c = 0; c < kNumPieceCaps; ++c) cnt[c] = 0;
+    // pieces under each cap and, last, segments; they fit 16 bits, since a
+    // batch at the minimum share has at most eight blocks for every workgroup
+    // of the grid
+    constexpr int kPacked = kNumPieceCaps / 2 + 1;
+    static_assert(kNumPieceCaps % 2 == 1, "the segments take the free half");
+    uint32_t cnt[kPacked] = {};
+    int longest = 0;
     for (int i = lo; i < hi; ++i) {
       const int seg = per == 1 ? sum : segment_len(p, i);
 #pragma unroll
-      for (int c = 0; c < kNumPieceCaps; ++c) cnt[c] += seg_pieces(seg, piece_cap(c));
+      for (int c = 0; c < kNumPieceCaps; ++c)
+        cnt[c / 2] += (uint32_t)seg_pieces(seg, piece_cap(c)) << (16 * (c % 2));
+      cnt[kPacked - 1] += seg > 0 ? 1u << 16 : 0u;
+      longest = max(longest, seg);
     }
-    int *red = loc + 8;  // [kNumPieceCaps][NW]
+    uint32_t *red = reinterpret_cast<uint32_t *>(loc + 8);  // [kPacked + 1][NW]
     const int lane = tid % kWave, wave = tid / kWave;
 #pragma unroll
-    for (int c = 0; c < kNumPieceCaps; ++c) {
-      const int v = wave_incl_scan(cnt[c]);
-      if (lane == kWave - 1) red[c * NW + wave] = v;
+    for (int c = 0; c <= kPacked; ++c) {
+      const int v = c < kPacked ? wave_incl_scan((int)cnt[c < kPacked ? c : 0]) : wave_max(longest);
+      if (lane == kWave - 1) red[c * NW + wave] = (uint32_t)v;
     }
     __syncthreads();
     // every piece needs a workgroup of the grid
     const int one_per_cu = min(p.num_cu, (int)gridDim.x);
-    for (int c = kNumPieceCaps - 1; c >= -1; --c) {
-      // the smallest cap with at most one piece per CU; failing that the
-      // smallest cap if its pieces fit the grid
-      const int cc = c < 0 ? 0 : c;
+    longest = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      longest = max(longest, (int)red[kPacked * NW + w]);
+    }
+    int pieces[kNumPieceCaps + 1];
+#pragma unroll
+    for (int c = 0; c <= kNumPieceCaps; ++c) {
       int t = 0;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) t += red[cc * NW + w];
-      if (c >= 0 ? t * p.hkv <= one_per_cu : t * p.hkv <= (int)gridDim.x && cap == 0)
-        cap = piece_cap(cc);
+      for (int w = 0; w < NW; ++w) t += (int)(red[c / 2 * NW + w] >> (16 * (c % 2)) & 0xFFFFu);
+      pieces[c] = t * p.hkv;
+    }
+#pragma unroll
+    for (int c = kNumPieceCaps - 1; c >= 0; --c)
+      if (pieces[c] <= one_per_cu || (c == 0 && cap == 0 && pieces[c] <= (int)gridDim.x))
+        cap = piece_cap(c);
+    // below eight blocks: a cap of c blocks leaves at most work / c pieces
+    // plus one per segment
+    const int spare = one_per_cu - pieces[kNumPieceCaps];
+    if (spare > 0) {
+      const int blocks = max(2, max((longest / kBlockKeys + kMaxMerge - 1) / kMaxMerge,
+                                    (work / kBlockKeys + spare - 1) / spare));
+      if (blocks < 8) cap = blocks * kBlockKeys;
     }
   }
   const bool seg_mode = cap > 0;
@@ -919,7 +957,7 @@ template <int D, int NW>
 __global__ __launch_bounds__(NW *kWave, 2) void attn_streamk_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(1024))) char buf[Ring<D, NW>::kBytes];
   __shared__ int ids[kSubPages];
-  __shared__ int lds_plan[2 * NW + 8 + kNumPieceCaps * NW];
+  __shared__ int lds_plan[2 * NW + 8 + (kNumPieceCaps / 2 + 2) * NW];
 
   const Share sh = plan_share<NW>(p, lds_plan);
   if (sh.start >= sh.end) return;
