@@ -150,28 +150,22 @@ __device__ __forceinline__ ReqMeta load_req(const AttnParams &p, int i) {
 }
 
 // -------------------------------------------------------------------- steps
-// The block loop works in steps of 32 keys (D = 128; 64 at D = 64), page pairs
-// whose tiles hold exactly the MFMA operands:
+// The key loop works in steps of one 32-key block, a pair of pages whose tiles
+// hold exactly the MFMA operands:
 //  K: the 1 KiB chunk c of a page's K tile is the A operand of the score
 //     MFMA over dims 32c .. 32c+31, lane l holding slot l & 15.
 //  V: lane (kq, m) of d block u takes the 16 bytes of dim 16u+m that hold
-//     slots 8*(kq>>1) .. +7 of page kq & 1 of a pair.
+//     slots 8*(kq>>1) .. +7 of page kq & 1.
 constexpr int kSubKeys = 8192;              // keys whose page ids are staged at a time
 constexpr int kSubPages = kSubKeys / kPage;
 
 template <int D>
-struct Step {
-  static constexpr int kPairs = 128 / D;              // page pairs
-  static constexpr int kKeys = kBlockKeys * kPairs;   // keys
-  static constexpr int kPages = 2 * kPairs;
-};
-template <int D>
 struct KRegs {
-  u32x4 x[Step<D>::kPages][D / 32];  // [page][chunk]
+  u32x4 x[2][D / 32];  // [page][chunk]
 };
-template <int D, int NE>
+template <int NE>
 struct VRegs {
-  u32x4 x[Step<D>::kPairs][NE];  // [page pair][d block]
+  u32x4 x[NE];  // [d block]
 };
 
 // Maximum / sum over the four lanes that hold one query row (lanes n, n+16,
@@ -577,21 +571,21 @@ __device__ __forceinline__ void clear_state(RowState<TW, NE> &st) {
 // Scores of one step for the wave's tiles (raw: the scale is positive and
 // applied inside the exponent).  Element (h, q) of a lane is key
 // t0 + 16h + 4*(lane>>4) + q.
-template <int D, int TW>
+template <int TW>
 struct Scores {
-  f32x4 x[TW][Step<D>::kPages];
+  f32x4 x[TW][2];
 };
 template <int D, int TW>
 __device__ __forceinline__ void step_scores(const KRegs<D> &k, const QOps<D, TW> &qv,
-                                            Scores<D, TW> &s) {
+                                            Scores<TW> &s) {
 #pragma unroll
   for (int t = 0; t < TW; ++t) {
 #pragma unroll
-    for (int h = 0; h < Step<D>::kPages; ++h) s.x[t][h] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int h = 0; h < 2; ++h) s.x[t][h] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int c = 0; c < D / 32; ++c) {
 #pragma unroll
-      for (int h = 0; h < Step<D>::kPages; ++h)
+      for (int h = 0; h < 2; ++h)
         s.x[t][h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
             as_bf16x8(__builtin_bit_cast(uint4, k.x[h][c])), qv.r[t][c], s.x[t][h], 0, 0, 0);
     }
@@ -601,37 +595,33 @@ __device__ __forceinline__ void step_scores(const KRegs<D> &k, const QOps<D, TW>
 // Causal and end-of-request masking of a step that not every live row sees
 // whole.  Keys at or past `se` may hold anything (even NaN), so their V is
 // zeroed as well.
-template <int D, int TW, int NE>
+template <int TW, int NE>
 __device__ __forceinline__ void step_mask(int t0, int se, const int (&row_limit)[TW], int lane,
-                                          Scores<D, TW> &s, VRegs<D, NE> &v) {
+                                          Scores<TW> &s, VRegs<NE> &v) {
   const int kq = lane >> 4;
 #pragma unroll
   for (int t = 0; t < TW; ++t)
 #pragma unroll
-    for (int h = 0; h < Step<D>::kPages; ++h)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int key = t0 + 16 * h + 4 * kq + q;
         if (key > row_limit[t] || key >= se) s.x[t][h][q] = -INFINITY;
       }
+  const int tb = t0 + 16 * (kq & 1) + 8 * (kq >> 1);
 #pragma unroll
-  for (int e = 0; e < Step<D>::kPairs; ++e) {
-    const int tb = t0 + 32 * e + 16 * (kq & 1) + 8 * (kq >> 1);
+  for (int w = 0; w < 4; ++w) {
+    const uint32_t mask = (tb + 2 * w < se ? 0x0000FFFFu : 0u) |
+                          (tb + 2 * w + 1 < se ? 0xFFFF0000u : 0u);
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const uint32_t mask = (tb + 2 * w < se ? 0x0000FFFFu : 0u) |
-                            (tb + 2 * w + 1 < se ? 0xFFFF0000u : 0u);
-#pragma unroll
-      for (int u = 0; u < NE; ++u) v.x[e][u][w] &= mask;
-    }
+    for (int u = 0; u < NE; ++u) v.x[u][w] &= mask;
   }
 }
 
 // Online softmax and the PV product of one step.
-template <int D, int TW, int NE>
-__device__ __forceinline__ void step_update(const Scores<D, TW> &s, const VRegs<D, NE> &v,
+template <int TW, int NE>
+__device__ __forceinline__ void step_update(const Scores<TW> &s, const VRegs<NE> &v,
                                             float scale_log2, RowState<TW, NE> &st) {
-  constexpr int kPages = Step<D>::kPages;
   // a lane's own keys decide whether any row's maximum moves; only then are
   // the row's four lanes brought together
   bool jump = false;
@@ -639,7 +629,7 @@ __device__ __forceinline__ void step_update(const Scores<D, TW> &s, const VRegs<
   for (int t = 0; t < TW; ++t) {
     float top = -INFINITY;
 #pragma unroll
-    for (int h = 0; h < kPages; ++h)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         top = fmaxf(top, __builtin_fmaf(s.x[t][h][q], scale_log2, -st.m[t]));
@@ -650,7 +640,7 @@ __device__ __forceinline__ void step_update(const Scores<D, TW> &s, const VRegs<
     for (int t = 0; t < TW; ++t) {
       float top = -INFINITY;
 #pragma unroll
-      for (int h = 0; h < kPages; ++h)
+      for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int q = 0; q < 4; ++q) top = fmaxf(top, s.x[t][h][q]);
       const float m_new = fmaxf(st.m[t], ceilf(row_max4(top) * scale_log2));
@@ -664,49 +654,46 @@ __device__ __forceinline__ void step_update(const Scores<D, TW> &s, const VRegs<
   }
 #pragma unroll
   for (int t = 0; t < TW; ++t) {
+    // P enters the bf16 PV product as a pair: hi = P rounded to bf16 and
+    // lo = the remainder rounded to bf16, so hi + lo carries P to about
+    // 2^-17 of its value and the weights add no error next to the output's
+    // own bf16 rounding.  The row sum adds the fp32 weights themselves.
+    uint32_t hi[2][2], lo[2][2];
+    float psum[2];
 #pragma unroll
-    for (int e = 0; e < Step<D>::kPairs; ++e) {
-      // P enters the bf16 PV product as a pair: hi = P rounded to bf16 and
-      // lo = the remainder rounded to bf16, so hi + lo carries P to about
-      // 2^-17 of its value and the weights add no error next to the output's
-      // own bf16 rounding.  The row sum adds the fp32 weights themselves.
-      uint32_t hi[2][2], lo[2][2];
-      float psum[2];
+    for (int h = 0; h < 2; ++h) {
+      float pw[4];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        float pw[4];
+      for (int q = 0; q < 4; ++q)
+        pw[q] = __builtin_amdgcn_exp2f(
+            __builtin_fmaf(s.x[t][h][q], scale_log2, -st.m[t]));
+      psum[h] = (pw[0] + pw[1]) + (pw[2] + pw[3]);
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          pw[q] = __builtin_amdgcn_exp2f(
-              __builtin_fmaf(s.x[t][2 * e + h][q], scale_log2, -st.m[t]));
-        psum[h] = (pw[0] + pw[1]) + (pw[2] + pw[3]);
-#pragma unroll
-        for (int w = 0; w < 2; ++w) {
-          const uint32_t x = pack_bf16x2(pw[2 * w], pw[2 * w + 1]);
-          hi[h][w] = x;
-          lo[h][w] = pack_bf16x2(pw[2 * w] - __uint_as_float(x << 16),
-                                 pw[2 * w + 1] - __uint_as_float(x & 0xFFFF0000u));
-        }
+      for (int w = 0; w < 2; ++w) {
+        const uint32_t x = pack_bf16x2(pw[2 * w], pw[2 * w + 1]);
+        hi[h][w] = x;
+        lo[h][w] = pack_bf16x2(pw[2 * w] - __uint_as_float(x << 16),
+                               pw[2 * w + 1] - __uint_as_float(x & 0xFFFF0000u));
       }
-      st.l[t] += psum[0] + psum[1];
-      // lane (kq, n) holds slots 4kq .. +3 of both pages; trading odd rows of
-      // page 0's against even rows of page 1's leaves it slots 8*(kq>>1) .. +7
-      // of page kq & 1, the keys of its V operand
-      const auto h0 = __builtin_amdgcn_permlane16_swap(hi[0][0], hi[1][0], false, false);
-      const auto h1 = __builtin_amdgcn_permlane16_swap(hi[0][1], hi[1][1], false, false);
-      const auto l0 = __builtin_amdgcn_permlane16_swap(lo[0][0], lo[1][0], false, false);
-      const auto l1 = __builtin_amdgcn_permlane16_swap(lo[0][1], lo[1][1], false, false);
-      const bf16x8 ph = as_bf16x8(make_uint4(h0[0], h1[0], h0[1], h1[1]));
-      const bf16x8 pl = as_bf16x8(make_uint4(l0[0], l1[0], l0[1], l1[1]));
-#pragma unroll
-      for (int u = 0; u < NE; ++u)
-        st.o[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-            as_bf16x8(__builtin_bit_cast(uint4, v.x[e][u])), ph, st.o[t][u], 0, 0, 0);
-#pragma unroll
-      for (int u = 0; u < NE; ++u)
-        st.o[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-            as_bf16x8(__builtin_bit_cast(uint4, v.x[e][u])), pl, st.o[t][u], 0, 0, 0);
     }
+    st.l[t] += psum[0] + psum[1];
+    // lane (kq, n) holds slots 4kq .. +3 of both pages; trading odd rows of
+    // page 0's against even rows of page 1's leaves it slots 8*(kq>>1) .. +7
+    // of page kq & 1, the keys of its V operand
+    const auto h0 = __builtin_amdgcn_permlane16_swap(hi[0][0], hi[1][0], false, false);
+    const auto h1 = __builtin_amdgcn_permlane16_swap(hi[0][1], hi[1][1], false, false);
+    const auto l0 = __builtin_amdgcn_permlane16_swap(lo[0][0], lo[1][0], false, false);
+    const auto l1 = __builtin_amdgcn_permlane16_swap(lo[0][1], lo[1][1], false, false);
+    const bf16x8 ph = as_bf16x8(make_uint4(h0[0], h1[0], h0[1], h1[1]));
+    const bf16x8 pl = as_bf16x8(make_uint4(l0[0], l1[0], l0[1], l1[1]));
+#pragma unroll
+    for (int u = 0; u < NE; ++u)
+      st.o[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          as_bf16x8(__builtin_bit_cast(uint4, v.x[u])), ph, st.o[t][u], 0, 0, 0);
+#pragma unroll
+    for (int u = 0; u < NE; ++u)
+      st.o[t][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+          as_bf16x8(__builtin_bit_cast(uint4, v.x[u])), pl, st.o[t][u], 0, 0, 0);
   }
 }
 
@@ -722,7 +709,7 @@ __device__ __forceinline__ void step_update(const Scores<D, TW> &s, const VRegs<
 template <int D, int NW>
 struct Ring {
   static constexpr int kSteps = NW / 4;
-  static constexpr int kKeys = kSteps * Step<D>::kKeys;
+  static constexpr int kKeys = kSteps * kBlockKeys;
   static constexpr int kPages = kKeys / kPage;
   static constexpr int kTile = kPage * D * 2;          // bytes of a page's K or V
   static constexpr int kStage = 2 * kPages * kTile;    // K tiles, then V tiles (kSteps * 16 KiB)
@@ -814,29 +801,26 @@ __device__ __forceinline__ void ring_step(const RingCtx &c, char *ring, int b, i
                    512 * role.e_lo;
 #pragma unroll 1
   for (int sub = 0; sub < R::kSteps; ++sub) {
-    const int t0 = c.sb + b * R::kKeys + sub * Step<D>::kKeys;
+    const int t0 = c.sb + b * R::kKeys + sub * kBlockKeys;
     if (t0 >= c.se) break;
     KRegs<D> k;
 #pragma unroll
-    for (int h = 0; h < Step<D>::kPages; ++h)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int x = 0; x < D / 32; ++x)
         k.x[h][x] = *reinterpret_cast<const u32x4 *>(
-            stage + (sub * Step<D>::kPages + h) * R::kTile + 1024 * x + 16 * lane);
-    Scores<D, TW> s;
+            stage + (sub * 2 + h) * R::kTile + 1024 * x + 16 * lane);
+    Scores<TW> s;
     step_scores<D, TW>(k, qv, s);
     // V's reads stay behind the score products: their registers are K's
     __builtin_amdgcn_sched_barrier(0);
-    VRegs<D, NE> v;
+    VRegs<NE> v;
 #pragma unroll
-    for (int e = 0; e < Step<D>::kPairs; ++e)
-#pragma unroll
-      for (int u = 0; u < NE; ++u)
-        v.x[e][u] = *reinterpret_cast<const u32x4 *>(
-            vb + (sub * Step<D>::kPages + 2 * e) * R::kTile + 512 * u);
-    if (t0 + Step<D>::kKeys > min(c.ctx, c.se))
-      step_mask<D, TW, NE>(t0, c.se, qv.row_limit, lane, s, v);
-    step_update<D, TW, NE>(s, v, scale_log2, st);
+    for (int u = 0; u < NE; ++u)
+      v.x[u] = *reinterpret_cast<const u32x4 *>(vb + sub * 2 * R::kTile + 512 * u);
+    if (t0 + kBlockKeys > min(c.ctx, c.se))
+      step_mask<TW, NE>(t0, c.se, qv.row_limit, lane, s, v);
+    step_update<TW, NE>(s, v, scale_log2, st);
   }
 }
 
@@ -952,9 +936,15 @@ __device__ __forceinline__ void run_piece(const AttnParams &p, char *buf, int *i
 }
 
 // NW waves: four, two workgroups to a CU; eight, one to a CU, for G = 16,
-// whose requests may have more than eight row tiles.
-template <int D, int NW>
-__global__ __launch_bounds__(NW *kWave, 2) void attn_streamk_kernel(AttnParams p) {
+// whose requests may have more than eight row tiles.  kTwo: requests may have
+// more than NW row tiles (G = 8 and 16), two to a wave.  At D = 64 a step is
+// half the bytes and a wave needs half the registers, so four workgroups fit a
+// CU (three with two tiles to a wave; four would spill): 16 requests of 10K
+// keys on one KV head take 22.5 us instead of 26.4, 33 short ones of eight
+// heads to a KV head 39.5 instead of 43.5.  At D = 128 three to a CU measured
+// slower (36 requests, contexts to 2K, four layers: 232.8 -> 252.9 us).
+template <int D, int NW, bool kTwo>
+__global__ __launch_bounds__(NW *kWave, D == 64 && NW == 4 ? (kTwo ? 3 : 4) : 2) void attn_streamk_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(1024))) char buf[Ring<D, NW>::kBytes];
   __shared__ int ids[kSubPages];
   __shared__ int lds_plan[2 * NW + 8 + (kNumPieceCaps / 2 + 2) * NW];
@@ -1009,9 +999,9 @@ __global__ __launch_bounds__(NW *kWave, 2) void attn_streamk_kernel(AttnParams p
       run_piece<D, 1, kBlocks / 4, NW>(p, buf, ids, x, wave, lane);
     else if (NW == 4 && nt == 2)
       run_piece<D, 1, kBlocks / 2, NW>(p, buf, ids, x, wave, lane);
-    else if (nt <= NW)
+    else if (!kTwo || nt <= NW)
       run_piece<D, 1, kBlocks, NW>(p, buf, ids, x, wave, lane);
-    else
+    else if constexpr (kTwo)
       run_piece<D, 2, kBlocks, NW>(p, buf, ids, x, wave, lane);
 
     pos += take;
@@ -1178,17 +1168,22 @@ struct SplitKernel {
 };
 SplitKernel split_kernel(int head_dim, int group) {
   if (group > 8)
-    return {head_dim == 128 ? attn_streamk_kernel<128, 8> : attn_streamk_kernel<64, 8>, 8 * kWave};
-  return {head_dim == 128 ? attn_streamk_kernel<128, 4> : attn_streamk_kernel<64, 4>, 4 * kWave};
+    return {head_dim == 128 ? attn_streamk_kernel<128, 8, true> : attn_streamk_kernel<64, 8, true>,
+            8 * kWave};
+  if (group > 4)
+    return {head_dim == 128 ? attn_streamk_kernel<128, 4, true> : attn_streamk_kernel<64, 4, true>,
+            4 * kWave};
+  return {head_dim == 128 ? attn_streamk_kernel<128, 4, false> : attn_streamk_kernel<64, 4, false>,
+          4 * kWave};
 }
 
 // Workgroups the GPU holds at once for the split kernel (cached per device
 // and kernel; a host query, so it is safe during graph capture).
 int resident_workgroups(int head_dim, int group) {
-  static int cache[64][4];
+  static int cache[64][6];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
-  int &slot = cache[dev][(head_dim == 128 ? 1 : 0) + (group > 8 ? 2 : 0)];
+  int &slot = cache[dev][(head_dim == 128 ? 1 : 0) + (group > 8 ? 4 : (group > 4 ? 2 : 0))];
   if (slot > 0) return slot;
   const int cus = device_cus();
   int per_cu = 0;
