@@ -240,16 +240,15 @@ hipError_t launch_accept(const void *logits, int dtype, const int32_t *cu,
   const dim3 grid(num_chunks, cap);
   timing_mark(kTimeArgmax, false, s);
   if (dtype == DSV_BF16)
-    hipLaunchKernelGGL(argmax_chunk_kernel<true>, grid, dim3(kThreads), 0, s, logits,
-                       cu, num_reqs, cap, vocab, num_chunks, best_val, best_idx);
+    launch_kernel(argmax_chunk_kernel<true>, grid, dim3(kThreads), s, logits, cu, num_reqs, cap,
+                  vocab, num_chunks, best_val, best_idx);
   else
-    hipLaunchKernelGGL(argmax_chunk_kernel<false>, grid, dim3(kThreads), 0, s, logits,
-                       cu, num_reqs, cap, vocab, num_chunks, best_val, best_idx);
+    launch_kernel(argmax_chunk_kernel<false>, grid, dim3(kThreads), s, logits, cu, num_reqs,
+                  cap, vocab, num_chunks, best_val, best_idx);
   timing_mark(kTimeArgmax, true, s);
   timing_mark(kTimePrefix, false, s);
-  hipLaunchKernelGGL(prefix_kernel, dim3(num_reqs), dim3(kWave), 0, s, cu, draft,
-                     accept_len, next_token, num_reqs, cap, num_chunks, best_val,
-                     best_idx);
+  launch_kernel(prefix_kernel, dim3(num_reqs), dim3(kWave), s, cu, draft, accept_len,
+                next_token, num_reqs, cap, num_chunks, best_val, best_idx);
   timing_mark(kTimePrefix, true, s);
   return hipGetLastError();
 }

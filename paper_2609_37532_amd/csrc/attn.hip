@@ -1237,13 +1237,13 @@ hipError_t launch_verify_attn(const AttnParams &p, int head_dim, hipStream_t s) 
                        p.num_reqs + 1);
   timing_mark(kTimeAttnSplit, false, s);
   const SplitKernel split = split_kernel(head_dim, p.group);
-  hipLaunchKernelGGL(split.fn, dim3(p.num_wg), dim3(split.threads), 0, s, p);
+  launch_kernel(split.fn, dim3(p.num_wg), dim3(split.threads), s, p);
   timing_mark(kTimeAttnSplit, true, s);
   timing_mark(kTimeAttnCombine, false, s);
   if (head_dim == 128)
-    hipLaunchKernelGGL(attn_combine_kernel<128>, grid_comb, dim3(kCombThreads), 0, s, p);
+    launch_kernel(attn_combine_kernel<128>, grid_comb, dim3(kCombThreads), s, p);
   else
-    hipLaunchKernelGGL(attn_combine_kernel<64>, grid_comb, dim3(kCombThreads), 0, s, p);
+    launch_kernel(attn_combine_kernel<64>, grid_comb, dim3(kCombThreads), s, p);
   timing_mark(kTimeAttnCombine, true, s);
   return hipGetLastError();
 }

@@ -4,6 +4,9 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <string.h>
+
+#include <type_traits>
 
 #include "dsv.h"
 
@@ -127,6 +130,53 @@ enum TimingKind {
 // Records a HIP event before (end = false) or after (end = true) a launch
 // when timing is on and the stream is not being captured.
 void timing_mark(int kind, bool end, hipStream_t s);
+
+// -------------------------------------------------------------------------
+// launches
+// -------------------------------------------------------------------------
+// One kernel launch with its arguments by value, so that it can be repeated.
+struct LaunchRecord {
+  static constexpr int kMaxArgs = 16, kMaxBytes = 256;
+  const void *fn;
+  dim3 grid, block;
+  int num_args;
+  uint16_t offset[kMaxArgs];
+  alignas(16) unsigned char bytes[kMaxBytes];
+};
+// Launches r on s; notes it too if this thread is capturing s through
+// dsv_graph_capture_begin.
+hipError_t enqueue(LaunchRecord &r, hipStream_t s);
+
+template <typename P>
+inline void pack_arg(LaunchRecord &r, size_t &used, P value) {
+  static_assert(std::is_trivially_copyable<P>::value && alignof(P) <= 16, "kernel argument");
+  used = (used + alignof(P) - 1) / alignof(P) * alignof(P);
+  r.offset[r.num_args++] = (uint16_t)used;
+  memcpy(r.bytes + used, &value, sizeof(P));
+  used += sizeof(P);
+}
+
+template <typename... P>
+struct ArgBytes {  // an upper bound of the packed size
+  static constexpr size_t value = (size_t(0) + ... + ((sizeof(P) + 15) / 16 * 16));
+};
+
+// Every kernel of the library is launched through this; as after a
+// triple-chevron launch, hipGetLastError has the outcome.
+template <typename... P, typename... A>
+inline void launch_kernel(void (*fn)(P...), dim3 grid, dim3 block, hipStream_t s,
+                                const A &...args) {
+  static_assert(sizeof...(P) == sizeof...(A) && sizeof...(P) <= LaunchRecord::kMaxArgs, "arguments");
+  static_assert(ArgBytes<P...>::value <= LaunchRecord::kMaxBytes, "argument bytes");
+  LaunchRecord r;
+  r.fn = reinterpret_cast<const void *>(fn);
+  r.grid = grid;
+  r.block = block;
+  r.num_args = 0;
+  size_t used = 0;
+  (pack_arg<P>(r, used, args), ...);
+  (void)enqueue(r, s);
+}
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 

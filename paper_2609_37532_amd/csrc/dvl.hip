@@ -374,7 +374,7 @@ hipError_t launch_dvl(const float *pred_logits, const int32_t *num_live,
   const int want = m_bs > n_bs ? (m_bs < kMaxReqs ? m_bs : kMaxReqs) : n_bs;
   const int threads = ((want + kWave - 1) / kWave) * kWave;
   timing_mark(kTimeDvl, false, s);
-  hipLaunchKernelGGL(dvl_kernel, dim3(1), dim3(threads), 0, s, a);
+  launch_kernel(dvl_kernel, dim3(1), dim3(threads), s, a);
   const hipError_t e = hipGetLastError();
   timing_mark(kTimeDvl, true, s);
   return e;

@@ -181,16 +181,16 @@ hipError_t launch_predictor(const float *features, const int32_t *num_live, cons
   const dim3 grid(slices, (n_bs + rt - 1) / rt);
   timing_mark(kTimePredictor, false, s);
   if (rt == 16)
-    hipLaunchKernelGGL(mlp_hidden_partial_kernel<16>, grid, dim3(kThreads), 0, s, features,
-                       num_live, w1, part, n_bs, in_dim);
+    launch_kernel(mlp_hidden_partial_kernel<16>, grid, dim3(kThreads), s, features, num_live,
+                  w1, part, n_bs, in_dim);
   else if (rt == 32)
-    hipLaunchKernelGGL(mlp_hidden_partial_kernel<32>, grid, dim3(kThreads), 0, s, features,
-                       num_live, w1, part, n_bs, in_dim);
+    launch_kernel(mlp_hidden_partial_kernel<32>, grid, dim3(kThreads), s, features, num_live,
+                  w1, part, n_bs, in_dim);
   else
-    hipLaunchKernelGGL(mlp_hidden_partial_kernel<64>, grid, dim3(kThreads), 0, s, features,
-                       num_live, w1, part, n_bs, in_dim);
-  hipLaunchKernelGGL(mlp_output_kernel, dim3(n_bs), dim3(kWave), 0, s, part, num_live, b1, w2,
-                     b2, out, n_bs, slices, out_dim);
+    launch_kernel(mlp_hidden_partial_kernel<64>, grid, dim3(kThreads), s, features, num_live,
+                  w1, part, n_bs, in_dim);
+  launch_kernel(mlp_output_kernel, dim3(n_bs), dim3(kWave), s, part, num_live, b1, w2, b2, out,
+                n_bs, slices, out_dim);
   const hipError_t e = hipGetLastError();
   timing_mark(kTimePredictor, true, s);
   return e;

@@ -80,8 +80,7 @@ extern "C" int dsv_read_probe(const void *buf, int32_t buf_tiles, const int32_t 
   if (!buf || !order || !sink) return DSV_ERR_NULL;
   if (buf_tiles < 1 || visits < 1 || grid < 1 || grid > 65535) return DSV_ERR_DIMS;
   if ((uintptr_t)buf & 15u) return DSV_ERR_UNSUPPORTED;
-  hipLaunchKernelGGL(read_probe_kernel, dim3(grid), dim3(kThreads), 0,
-                     (hipStream_t)hip_stream, (const u32x4 *)buf, buf_tiles, order, visits,
-                     sink);
+  launch_kernel(read_probe_kernel, dim3(grid), dim3(kThreads), (hipStream_t)hip_stream, (const
+                u32x4 *)buf, buf_tiles, order, visits, sink);
   return hipGetLastError() == hipSuccess ? DSV_OK : DSV_ERR_HIP;
 }

@@ -483,21 +483,21 @@ hipError_t launch_accept_stochastic(const void *logits, int dtype, const int32_t
   const dim3 grid(num_chunks, cap);
   timing_mark(kTimeSampleStats, false, s);
   if (dtype == DSV_BF16)
-    hipLaunchKernelGGL(softmax_stats_kernel<true>, grid, dim3(kThreads), 0, s, logits, cu,
-                       num_reqs, cap, vocab, num_chunks, scale_log2, stat_m, stat_s);
+    launch_kernel(softmax_stats_kernel<true>, grid, dim3(kThreads), s, logits, cu, num_reqs,
+                  cap, vocab, num_chunks, scale_log2, stat_m, stat_s);
   else
-    hipLaunchKernelGGL(softmax_stats_kernel<false>, grid, dim3(kThreads), 0, s, logits, cu,
-                       num_reqs, cap, vocab, num_chunks, scale_log2, stat_m, stat_s);
+    launch_kernel(softmax_stats_kernel<false>, grid, dim3(kThreads), s, logits, cu, num_reqs,
+                  cap, vocab, num_chunks, scale_log2, stat_m, stat_s);
   timing_mark(kTimeSampleStats, true, s);
   timing_mark(kTimeSampleDraw, false, s);
   if (dtype == DSV_BF16)
-    hipLaunchKernelGGL(stochastic_prefix_kernel<true>, dim3(num_reqs), dim3(kThreads), 0, s,
-                       logits, cu, draft, uniforms, accept_len, next_token, num_reqs, cap,
-                       vocab, num_chunks, scale_log2, stat_m, stat_s);
+    launch_kernel(stochastic_prefix_kernel<true>, dim3(num_reqs), dim3(kThreads), s, logits, cu,
+                  draft, uniforms, accept_len, next_token, num_reqs, cap, vocab, num_chunks,
+                  scale_log2, stat_m, stat_s);
   else
-    hipLaunchKernelGGL(stochastic_prefix_kernel<false>, dim3(num_reqs), dim3(kThreads), 0, s,
-                       logits, cu, draft, uniforms, accept_len, next_token, num_reqs, cap,
-                       vocab, num_chunks, scale_log2, stat_m, stat_s);
+    launch_kernel(stochastic_prefix_kernel<false>, dim3(num_reqs), dim3(kThreads), s, logits,
+                  cu, draft, uniforms, accept_len, next_token, num_reqs, cap, vocab, num_chunks,
+                  scale_log2, stat_m, stat_s);
   timing_mark(kTimeSampleDraw, true, s);
   return hipGetLastError();
 }
