@@ -118,20 +118,6 @@ __device__ __forceinline__ void wave_merge(float &m, float &s) {
   dpp_merge<0x143, 0xc>(m, s);
 }
 
-template <bool kBf16>
-__device__ __forceinline__ void acc_vec(u32x4 x, float c, float &m, float &s) {
-  if (kBf16) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      acc(m, s, scaled(bf16_lo(x[q]), c));
-      acc(m, s, scaled(bf16_hi(x[q]), c));
-    }
-  } else {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) acc(m, s, scaled(__uint_as_float(x[q]), c));
-  }
-}
-
 // Per (chunk, live row): max of logits * c and sum of exp2(logits * c - max).
 template <bool kBf16>
 __global__ __launch_bounds__(kThreads) void softmax_stats_kernel(
@@ -156,13 +142,16 @@ __global__ __launch_bounds__(kThreads) void softmax_stats_kernel(
   if (tid < head) acc(m, s, scaled(elem<kBf16>(row, begin + tid), c));
   if (tid < end - ve) acc(m, s, scaled(elem<kBf16>(row, ve + tid), c));
   const u32x4 *vp = (const u32x4 *)(row + (size_t)vb * kEs);
-  if (nvec == kThreads * kUnroll) {
-    // full chunk: the values sit in registers, so take their maximum first
-    // and then one exponential each
+  if (nvec > 0) {
+    // Every load of the chunk in flight at once, the values kept in registers:
+    // their maximum first and then one exponential each.  Vectors past the
+    // chunk's last (its row starts off 16 bytes, or it is the row's last
+    // chunk) read the last again and count as -inf.
+    constexpr int kN = kUnroll * kVec;
     u32x4 x[kUnroll];
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) x[u] = __builtin_nontemporal_load(vp + u * kThreads + tid);
-    constexpr int kN = kUnroll * kVec;
+    for (int u = 0; u < kUnroll; ++u)
+      x[u] = __builtin_nontemporal_load(vp + min(u * kThreads + tid, nvec - 1));
     float y[kN];
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
@@ -176,6 +165,14 @@ __global__ __launch_bounds__(kThreads) void softmax_stats_kernel(
         }
       }
     }
+    if (nvec < kThreads * kUnroll) {
+#pragma unroll
+      for (int u = 0; u < kUnroll; ++u)
+        if (u * kThreads + tid >= nvec) {
+#pragma unroll
+          for (int q = 0; q < kVec; ++q) y[u * kVec + q] = -INFINITY;
+        }
+    }
     float lm = y[0];
 #pragma unroll
     for (int q = 1; q < kN; ++q) lm = fmaxf(lm, y[q]);
@@ -185,9 +182,6 @@ __global__ __launch_bounds__(kThreads) void softmax_stats_kernel(
       for (int q = 0; q < kN; ++q) ls += fexp2(y[q] - lm);
     }
     merge(m, s, lm, ls);
-  } else {
-    for (int q = tid; q < nvec; q += kThreads)
-      acc_vec<kBf16>(__builtin_nontemporal_load(vp + q), c, m, s);
   }
   wave_merge(m, s);  // complete in lane 63
   __shared__ float sm[kThreads / kWave], ss[kThreads / kWave];
