@@ -7,8 +7,8 @@
 //
 // How: the first layer is a small GEMM, [N x in_dim] x [in_dim x 64], split
 // over K so that each workgroup reads its slice of W1 once for a tile of 16,
-// 32 or 64 requests (the smallest that holds the bucket, up to 64): the W1
-// slice and the feature tile go to LDS, and each thread accumulates one
+// 32 or 64 requests (the smallest that leaves every workgroup resident): the
+// W1 slice and the feature tile go to LDS, and each thread accumulates one
 // hidden unit for a quarter of the tile's requests, reading features as
 // LDS broadcasts.  Partial sums go to a workspace in
 // slice order; a second kernel, one wave per request, adds them in that
@@ -26,9 +26,19 @@ constexpr int kThreads = 256;
 constexpr int kRowGroups = kThreads / kH;  // 4: one per wave
 constexpr int kLdsStride = kKT + 4;        // keeps float4 rows aligned
 
-// Requests per tile: 16, 32 or 64, the smallest that holds the bucket (up
-// to 64), so a small bucket does not multiply zero rows.
-int tile_rows(int n_bs) { return n_bs <= 16 ? 16 : (n_bs <= 32 ? 32 : 64); }
+// Requests per tile: the smallest of 16, 32 and 64 that keeps the first kernel
+// at no more than kMaxTiles workgroups (two to a CU, all resident at once).
+// Smaller tiles spread the products over more CUs, and reread the W1 slices
+// from L2; a row's arithmetic is the same in every tile.  With 1,735 features,
+// predictor + DVL, tiles of 16 / 32 / 64 requests: 32 requests 17.7 / 20.0 /
+// - us, 64: 14.9 / - / 18.7, 128: 21.9 / - / 25.4, 256: 23.3 / - / 24.1, 512:
+// 35.9 / - / 32.7.
+constexpr int kMaxTiles = 512;
+int tile_rows(int n_bs, int slices) {
+  int rows = 16;
+  while (rows < 64 && (long long)slices * ((n_bs + rows - 1) / rows) > kMaxTiles) rows *= 2;
+  return rows;
+}
 
 __device__ __forceinline__ int live_count(const int32_t *num_live, int n_bs) {
   const int n = *num_live;
@@ -177,7 +187,7 @@ hipError_t launch_predictor(const float *features, const int32_t *num_live, cons
                             int32_t n_bs, int32_t in_dim, int32_t out_dim, float *part,
                             hipStream_t s) {
   const int slices = (in_dim + kKT - 1) / kKT;
-  const int rt = tile_rows(n_bs);
+  const int rt = tile_rows(n_bs, slices);
   const dim3 grid(slices, (n_bs + rt - 1) / rt);
   timing_mark(kTimePredictor, false, s);
   if (rt == 16)
