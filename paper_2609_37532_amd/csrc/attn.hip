@@ -812,8 +812,6 @@ __device__ __forceinline__ void ring_step(const RingCtx &c, char *ring, int b, i
             stage + (sub * 2 + h) * R::kTile + 1024 * x + 16 * lane);
     Scores<TW> s;
     step_scores<D, TW>(k, qv, s);
-    // V's reads stay behind the score products: their registers are K's
-    __builtin_amdgcn_sched_barrier(0);
     VRegs<NE> v;
 #pragma unroll
     for (int u = 0; u < NE; ++u)
