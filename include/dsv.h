@@ -373,7 +373,7 @@ int dsv_predictor_forward(const float *features, const int32_t *num_live, const 
  *                    sentinels).
  *   bucket_reqs      N_bs, host value in [1, DSV_DVL_MAX_REQS].
  *   block_width      W, host value, even, in [2, DSV_MAX_QLEN].
- * One workgroup; no workspace; capturable like every other call.
+ * No workspace; capturable like every other call.
  */
 #define DSV_DVL_MAX_REQS 1024
 int dsv_dvl_allocate_pack(const float *pred_logits, const int32_t *num_live,
@@ -397,7 +397,9 @@ int dsv_dvl_allocate_pack(const float *pred_logits, const int32_t *num_live,
  *  dsv_graph_capture_end    ends capture and instantiates; *graph_exec
  *                           receives an opaque handle owned by the caller
  *                           (NULL on failure).
- *  dsv_graph_replay         enqueues one replay on `hip_stream`.
+ *  dsv_graph_replay         enqueues one replay on `hip_stream`.  A graph that
+ *                           holds nothing but up to 16 of the library's own
+ *                           launches is replayed as those launches.
  *  dsv_graph_destroy        releases the handle.
  * All return a dsv_status.
  */

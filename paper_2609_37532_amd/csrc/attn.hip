@@ -61,11 +61,11 @@
 //   B=32, 64 / 8 heads, lengths about 8, contexts to 16K (1.2 GB): HBM, with
 //     the vector units close behind; 343 -> 228, 5.3 TB/s
 //   B=24, 32 / 2 heads, full blocks, contexts to 6K: the matrix and vector
-//     units (16 tiles to a key), then 33 MB of partials; 104 -> 62
-//   B=32, head_dim 64, contexts to 8K (0.3 GB): HBM; 60.7 -> 59.0
+//     units (16 tiles to a key), then 33 MB of partials; 104 -> 59
+//   B=32, head_dim 64, contexts to 8K (0.3 GB): HBM; 60.7 -> 58.0, 5.2 TB/s
 //   B=8, full blocks, contexts to 2K (40 MB): the chain from launch to the
-//     last block; 23.4 -> 22.1
-//   B=1, full block, context 700 (3 MB): the same; 16.9 -> 14.4
+//     last block; 23.4 -> 20.6
+//   B=1, full block, context 700 (3 MB): the same; 16.9 -> 13.2
 #include "dsv_internal.h"
 
 #include <math.h>
@@ -838,8 +838,7 @@ __device__ __forceinline__ void ring_run(const RingCtx &c, char *ring, int wave,
   }
   for (int b = 0; b < c.ns; b += kStages) {
     ring_step<D, TW, NE, NW, 0>(c, ring, b, wave, lane, r[0], qv, role, scale_log2, st);
-    ring_step<D, TW, NE, NW, 1>(c, ring, b + 1, wave, lane, r[1], qv, role, scale_log2,
-                                        st);
+    ring_step<D, TW, NE, NW, 1>(c, ring, b + 1, wave, lane, r[1], qv, role, scale_log2, st);
     ring_step<D, TW, NE, NW, 2>(c, ring, b + 2, wave, lane, r[2], qv, role, scale_log2, st);
   }
 }
