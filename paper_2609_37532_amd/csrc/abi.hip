@@ -109,13 +109,25 @@ Recording take_recording(hipStream_t s) {
   return Recording{s, 0, false, {}};
 }
 
-// Id of the capture that stream s is in (0: none).
+// Id of the capture that stream s is in (0: none).  A query that fails leaves
+// no error behind for the next launch to report.
 unsigned long long capture_id(hipStream_t s) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   unsigned long long id = 0;
-  if (hipStreamGetCaptureInfo(s, &cs, &id) != hipSuccess || cs != hipStreamCaptureStatusActive)
+  if (hipStreamGetCaptureInfo(s, &cs, &id) != hipSuccess) {
+    (void)hipGetLastError();
     return 0;
-  return id;
+  }
+  return cs == hipStreamCaptureStatusActive ? id : 0;
+}
+
+bool not_capturing(hipStream_t s) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return cs == hipStreamCaptureStatusNone;
 }
 
 // Whether graph g is exactly the recorded launches: as many nodes, all of them
@@ -392,9 +404,8 @@ int dsv_graph_replay(void *graph_exec, void *hip_stream) {
   // launches go to the current device, and a stream that is itself being
   // captured is given the graph
   int dev = -1;
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (!g->direct.empty() && hipGetDevice(&dev) == hipSuccess && dev == g->device &&
-      hipStreamIsCapturing(s, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) {
+      not_capturing(s)) {
     for (LaunchRecord r : g->direct)
       if (launch_record(r, s) != hipSuccess) return DSV_ERR_HIP;
     return DSV_OK;
