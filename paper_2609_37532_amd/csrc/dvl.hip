@@ -330,42 +330,22 @@ __global__ __launch_bounds__(kMaxReqs) void dvl_kernel(DvlArgs a) {
     if (j < k && off + j < m_bs) s_owner[off + j] = (uint16_t)tid;
   __syncthreads();
 
-  // ---- packing (Eq. (11)) and tail placeholders.  The workgroup packs rows
-  // row0 .. row1-1, its threads rows row0 + tid + u * nthr.  Sources are
-  // resolved first, then all loads are issued, then all stores; a placeholder
-  // row loads row 0 and discards it.
+  // ---- packing (Eq. (11)) and tail placeholders, one row a thread (a
+  // workgroup has at least as many threads as rows: up to 512, and no fewer
+  // than the bucket's rows below that).  A placeholder row loads row 0 and
+  // discards it.
   const int live_rows = total < m_bs ? total : m_bs;
   const int share = (m_bs + (int)gridDim.x - 1) / (int)gridDim.x;
-  const int row0 = min(m_bs, (int)blockIdx.x * share), row1 = min(m_bs, row0 + share);
-  int src[kMaxW / 2];
-#pragma unroll
-  for (int u = 0; u < kMaxW / 2; ++u) {
-    const int s = row0 + tid + u * nthr;
-    src[u] = -1;
-    if (s < row1 && s < live_rows) {
-      const int i = s_owner[s];
-      src[u] = i * w + (s - s_off[i]);
-    }
-  }
-  int tv[kMaxW / 2], pv[kMaxW / 2], rv[kMaxW / 2];
-#pragma unroll
-  for (int u = 0; u < kMaxW / 2; ++u) {
-    if (row0 + u * nthr < row1) {  // uniform
-      const int i = src[u] < 0 ? 0 : src[u];
-      tv[u] = a.tokens[i];
-      pv[u] = a.positions[i];
-      rv[u] = a.kv_refs[i];
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < kMaxW / 2; ++u) {
-    const int s = row0 + tid + u * nthr;
-    if (s < row1) {
-      const bool real = src[u] >= 0;
-      a.ptok[s] = real ? tv[u] : 0;
-      a.ppos[s] = real ? pv[u] : 0;
-      a.pref[s] = real ? rv[u] : ref0;
-    }
+  const int row0 = (int)blockIdx.x * share, row1 = min(m_bs, row0 + share);
+  const int s = row0 + tid;
+  if (s < row1) {
+    const bool real = s < live_rows;
+    const int i = real ? s_owner[s] : 0;
+    const int src = real ? i * w + (s - s_off[i]) : 0;
+    const int tv = a.tokens[src], pv = a.positions[src], rv = a.kv_refs[src];
+    a.ptok[s] = real ? tv : 0;
+    a.ppos[s] = real ? pv : 0;
+    a.pref[s] = real ? rv : ref0;
   }
 }
 
