@@ -189,3 +189,22 @@ def dvl_sweep_case(seed):
 @pytest.mark.parametrize("seed", range(24))
 def test_random_sweep(seed):
     check(dvl_sweep_case(seed), "sweep%d" % seed)
+
+
+@pytest.mark.parametrize("n_bs,w", [(1, 2), (33, 16), (1024, 16)])
+def test_scores_at_hard_logits(n_bs, w):
+    # the kernel's short sigmoid decides x >= -80 unless y sits within 1e-12
+    # of a rounding boundary: logits beyond and at that limit, specials, and
+    # ones picked next to boundaries (all bit-exact, as everywhere here)
+    rng = np.random.default_rng(n_bs)
+    x = rng.uniform(-30, 30, size=1 << 20).astype(np.float32)
+    y = 1.0 / (1.0 + np.exp(-x.astype(np.float64)))
+    near = x[(y * (1 - 1e-12)).astype(np.float32) != (y * (1 + 1e-12)).astype(np.float32)]
+    edge = np.float32([80, 1000, 3e38, np.inf, 0.0, 1e-30, 1e-45, 17.5, 36.0, 87.5, 104.5, 150])
+    edge = np.concatenate([edge, np.nextafter(edge[:1], np.float32(np.inf))])
+    pool = np.concatenate([near[:40], edge, -edge, np.float32([np.nan])])
+    assert near.size > 3
+    d = W.make_dvl_inputs(rng, n_bs=n_bs, n_live=n_bs, width=w)
+    # a request's running minimum would hide most values: descending rows
+    d.pred_logits[...] = -np.sort(-rng.choice(pool, size=d.pred_logits.shape), axis=1)
+    check(d, "hard logits")
