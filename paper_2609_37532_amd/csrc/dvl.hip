@@ -266,6 +266,7 @@ __global__ __launch_bounds__(kMaxReqs) void dvl_kernel(DvlArgs a) {
     // it is taken the remaining passes are skipped.
     uint32_t prefix = flip & 0x80000000u;
     int fshift = 31;
+    uint32_t match = valid;  // this thread's candidates under the prefix
 #pragma unroll
     for (int pass = 0; pass < 4; ++pass) {
       const int shift = pass == 3 ? 0 : 23 - 8 * pass;
@@ -274,28 +275,55 @@ __global__ __launch_bounds__(kMaxReqs) void dvl_kernel(DvlArgs a) {
       const uint32_t dmask = (1u << width) - 1u;
       uint32_t *hist = s_hist[pass];
       // histogram of the next digit among candidates under the prefix; runs
-      // of equal digits are added with one atomic
-      uint32_t match = 0;
-      uint32_t dig[kMaxW - 1];
+      // of equal digits are added with one atomic.  From the third pass on few
+      // candidates are left: a thread walks the ones it had before and reads
+      // their keys back from LDS, where a pass in the first form costs 15
+      // elements' worth of instructions whatever is left (1024 requests 22.35
+      // -> 20.21 us, predictor and DVL at 32 16.25 -> 15.78; logits on a 0.5
+      // grid 29.8 -> 26.5, 1024 identical requests 31.4 -> 30.9 and 32.2 ->
+      // 32.5).
+      if (pass < 2) {
+        uint32_t dig[kMaxW - 1];
+        uint32_t now = 0;
 #pragma unroll
-      for (int u = 0; u < kMaxW - 1; ++u) {
-        if (u < per) {
-          dig[u] = (key[u] >> shift) & dmask;
-          match |= (((valid >> u) & 1u) && (key[u] & hi) == (prefix & hi)) ? (1u << u) : 0u;
+        for (int u = 0; u < kMaxW - 1; ++u) {
+          if (u < per) {
+            dig[u] = (key[u] >> shift) & dmask;
+            now |= (((match >> u) & 1u) && (key[u] & hi) == (prefix & hi)) ? (1u << u) : 0u;
+          }
         }
-      }
-      int start = 0;
+        match = now;
+        int start = 0;
 #pragma unroll
-      for (int u = 0; u < kMaxW - 1; ++u) {
-        if (u < per) {
-          const bool m = (match >> u) & 1u;
-          const bool opens =
-              m && (u == 0 || !((match >> (u - 1)) & 1u) || dig[u - 1] != dig[u]);
-          start = opens ? u : start;
-          const bool closes = m && (u + 1 == per || !((match >> (u + 1)) & 1u) ||
-                                    dig[u + 1 < kMaxW - 1 ? u + 1 : u] != dig[u]);
-          if (closes) atomicAdd(&hist[dig[u]], (uint32_t)(u - start + 1));
+        for (int u = 0; u < kMaxW - 1; ++u) {
+          if (u < per) {
+            const bool m = (match >> u) & 1u;
+            const bool opens =
+                m && (u == 0 || !((match >> (u - 1)) & 1u) || dig[u - 1] != dig[u]);
+            start = opens ? u : start;
+            const bool closes = m && (u + 1 == per || !((match >> (u + 1)) & 1u) ||
+                                      dig[u + 1 < kMaxW - 1 ? u + 1 : u] != dig[u]);
+            if (closes) atomicAdd(&hist[dig[u]], (uint32_t)(u - start + 1));
+          }
         }
+      } else {
+        uint32_t now = 0, last = 0, run = 0;
+        for (uint32_t left = match; left != 0; left &= left - 1) {
+          const int u = __builtin_ctz(left);
+          const uint32_t x = __float_as_uint(s_val[e0 + u]) ^ flip;
+          if ((x & hi) == (prefix & hi)) {
+            now |= 1u << u;
+            const uint32_t d = (x >> shift) & dmask;
+            if (d != last && run != 0) {
+              atomicAdd(&hist[last], run);
+              run = 0;
+            }
+            last = d;
+            ++run;
+          }
+        }
+        if (run != 0) atomicAdd(&hist[last], run);
+        match = now;
       }
       __syncthreads();
       // every wave finds the digit holding the want-th largest key (lane L
@@ -332,10 +360,10 @@ __global__ __launch_bounds__(kMaxReqs) void dvl_kernel(DvlArgs a) {
     // key above it is taken, and the first `want` keys inside it in element
     // (request-major) order -- all of them unless the bucket is one value.
     int eq = 0;
-#pragma unroll
-    for (int u = 0; u < kMaxW - 1; ++u)
-      if (u < per && ((valid >> u) & 1u))
-        eq += (key[u] >> fshift) == (prefix >> fshift) ? 1 : 0;
+    for (uint32_t left = match; left != 0; left &= left - 1) {
+      const uint32_t x = __float_as_uint(s_val[e0 + __builtin_ctz(left)]) ^ flip;
+      eq += (x >> fshift) == (prefix >> fshift) ? 1 : 0;
+    }
     int eq_total;
     int rank = block_excl_scan(eq, s_wave[1], &eq_total);
     // per-request totals of taken elements, one atomic per run of a request
