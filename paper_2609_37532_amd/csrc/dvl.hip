@@ -275,24 +275,19 @@ __global__ __launch_bounds__(kMaxReqs) void dvl_kernel(DvlArgs a) {
       const uint32_t dmask = (1u << width) - 1u;
       uint32_t *hist = s_hist[pass];
       // histogram of the next digit among candidates under the prefix; runs
-      // of equal digits are added with one atomic.  From the third pass on few
-      // candidates are left: a thread walks the ones it had before and reads
+      // of equal digits are added with one atomic.  From the second pass on
+      // few candidates are left: a thread walks the ones it had before and reads
       // their keys back from LDS, where a pass in the first form costs 15
-      // elements' worth of instructions whatever is left (1024 requests 22.35
-      // -> 20.21 us, predictor and DVL at 32 16.25 -> 15.78; logits on a 0.5
-      // grid 29.8 -> 26.5, 1024 identical requests 31.4 -> 30.9 and 32.2 ->
-      // 32.5).
-      if (pass < 2) {
+      // elements' worth of instructions whatever is left (walking from the
+      // third pass on, 1024 requests 22.35 -> 20.21 us, predictor and DVL at 32
+      // 16.25 -> 15.78; from the second, 19.32 -> 18.67 and 15.37 -> 15.19;
+      // both, 1024 requests with logits on a 0.5 grid 29.8 -> 26.4, identical
+      // ones 31.4 -> 30.7 and 32.2 -> 32.4).
+      if (pass == 0) {  // every key has the prefix, bit 31
         uint32_t dig[kMaxW - 1];
-        uint32_t now = 0;
 #pragma unroll
-        for (int u = 0; u < kMaxW - 1; ++u) {
-          if (u < per) {
-            dig[u] = (key[u] >> shift) & dmask;
-            now |= (((match >> u) & 1u) && (key[u] & hi) == (prefix & hi)) ? (1u << u) : 0u;
-          }
-        }
-        match = now;
+        for (int u = 0; u < kMaxW - 1; ++u)
+          if (u < per) dig[u] = (key[u] >> shift) & dmask;
         int start = 0;
 #pragma unroll
         for (int u = 0; u < kMaxW - 1; ++u) {
