@@ -397,15 +397,20 @@ int dsv_dvl_allocate_pack(const float *pred_logits, const int32_t *num_live,
  *  dsv_graph_capture_end    ends capture and instantiates; *graph_exec
  *                           receives an opaque handle owned by the caller
  *                           (NULL on failure).
- *  dsv_graph_replay         enqueues one replay on `hip_stream`.  A graph that
- *                           holds nothing but up to 16 of the library's own
- *                           launches is replayed as those launches.
+ *  dsv_graph_replay         enqueues one replay on `hip_stream`.  A graph of at
+ *                           most six of the library's launches and nothing else
+ *                           is replayed as those launches.  After DSV_ERR_HIP a
+ *                           part of the replay may have been enqueued.
+ *  dsv_graph_direct_launches
+ *                           the launches that a replay makes in place of the
+ *                           graph, 0 if it launches the graph (for tests).
  *  dsv_graph_destroy        releases the handle.
- * All return a dsv_status.
+ * The others return a dsv_status.
  */
 int dsv_graph_capture_begin(void *hip_stream);
 int dsv_graph_capture_end(void *hip_stream, void **graph_exec);
 int dsv_graph_replay(void *graph_exec, void *hip_stream);
+int dsv_graph_direct_launches(const void *graph_exec);
 int dsv_graph_destroy(void *graph_exec);
 
 /*

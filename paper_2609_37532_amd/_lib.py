@@ -74,6 +74,7 @@ def load():
         "dsv_graph_capture_begin": (ctypes.c_int, [P]),
         "dsv_graph_capture_end": (ctypes.c_int, [P, ctypes.POINTER(ctypes.c_void_p)]),
         "dsv_graph_replay": (ctypes.c_int, [P, P]),
+        "dsv_graph_direct_launches": (ctypes.c_int, [P]),
         "dsv_graph_destroy": (ctypes.c_int, [P]),
         "dsv_read_probe": (ctypes.c_int, [P, I32, P, I32, P, I32, P]),
         "dsv_timing_start": (ctypes.c_int, [I32]),

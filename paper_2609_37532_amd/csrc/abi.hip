@@ -79,22 +79,29 @@ thread_local std::vector<Recording> t_recordings;
 
 // A captured graph.  A graph that is nothing but a short sequence of the
 // library's own launches is replayed by making those launches again:
-// hipGraphLaunch takes about 13 us of host time and 4 us of the GPU's on top
-// of such kernels (greedy acceptance, two kernels, back to back: 15.2 us a
-// replay, 10.3 us as launches; predictor and DVL, three: 23.4 and 18.6; the
-// attention of four short layers, eight: 54.7 and 51.3), a launch about 2 us
-// of the host's.  Longer graphs, and graphs that hold anything else, are
-// launched as graphs: 4 us is below 1% of them, and the host is spared.
-constexpr size_t kMaxDirect = 16;
+// hipGraphLaunch takes 14 to 25 us of host time and leaves the GPU idle for 4 us,
+// a launch takes 2 us of the host's.  As a graph and as launches, us back to
+// back / until done / of host time: DVL at 1024 requests, one launch, 23.6 / 34.7
+// / 15.0 and 18.9 / 29.4 / 3.0; greedy acceptance, two, 16.0 / 35.8 / 23.6 and
+// 10.4 / 21.0 / 5.2; acceptance of one request three times, six, 23.1 / 33.7 /
+// 20.1 and 19.3 / 28.1 / 13.2; attention of three short layers, six, 40.4 /
+// 51.7 / 15.3 and 36.5 / 47.0 / 12.6.  From eight on the launches cost the caller more
+// than the graph does, and short ones the GPU too: acceptance four times, eight,
+// 28.0 / 38.6 / 21.3 and 25.2 / 47.6 / 25.3; attention of four layers, eight,
+// 52.4 / 63.7 / 15.7 and 48.7 / 59.5 / 22.1; of eight, sixteen, 101.0 / 112.9 /
+// 17.9 and 98.8 / 109.9 / 42.4.  Longer graphs, and graphs that hold anything
+// else, are launched as graphs.
+constexpr size_t kMaxDirect = 6;
 struct Graph {
   hipGraphExec_t exec;
-  int device;
+  int device;                        // of the launches
   std::vector<LaunchRecord> direct;  // empty: launch exec
 };
 
-hipError_t launch_record(LaunchRecord &r, hipStream_t s) {
+hipError_t launch_record(const LaunchRecord &r, hipStream_t s) {
   void *args[LaunchRecord::kMaxArgs];
-  for (int n = 0; n < r.num_args; ++n) args[n] = r.bytes + r.offset[n];
+  for (int n = 0; n < r.num_args; ++n)
+    args[n] = const_cast<unsigned char *>(r.bytes) + r.offset[n];
   return hipLaunchKernel(r.fn, r.grid, r.block, args, 0, s);
 }
 
@@ -137,21 +144,21 @@ bool is_recorded(hipGraph_t g, const Recording &r) {
   if (!r.whole || r.launches.empty() || r.launches.size() > kMaxDirect) return false;
   hipGraphNode_t nodes[kMaxDirect];
   size_t n = 0;
-  if (hipGraphGetNodes(g, nullptr, &n) != hipSuccess || n != r.launches.size()) return false;
-  if (hipGraphGetNodes(g, nodes, &n) != hipSuccess || n != r.launches.size()) return false;
-  for (size_t i = 0; i < n; ++i) {
+  bool ok = hipGraphGetNodes(g, nullptr, &n) == hipSuccess && n == r.launches.size();
+  ok = ok && hipGraphGetNodes(g, nodes, &n) == hipSuccess && n == r.launches.size();
+  for (size_t i = 0; ok && i < n; ++i) {
     hipGraphNodeType type;
-    if (hipGraphNodeGetType(nodes[i], &type) != hipSuccess || type != hipGraphNodeTypeKernel)
-      return false;
+    ok = hipGraphNodeGetType(nodes[i], &type) == hipSuccess && type == hipGraphNodeTypeKernel;
   }
-  return true;
+  if (!ok) (void)hipGetLastError();
+  return ok;
 }
 
 }  // namespace
 
 namespace dsv {
 
-hipError_t enqueue(LaunchRecord &r, hipStream_t s) {
+hipError_t enqueue(const LaunchRecord &r, hipStream_t s) {
   const hipError_t e = launch_record(r, s);
   if (e != hipSuccess) return e;
   for (Recording &rec : t_recordings)
@@ -385,8 +392,9 @@ int dsv_graph_capture_end(void *hip_stream, void **graph_exec) {
   hipGraphExec_t ex = nullptr;
   const hipError_t e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
   Graph *out = e == hipSuccess ? new (std::nothrow) Graph{ex, -1, {}} : nullptr;
-  if (out && is_recorded(g, rec) && hipGetDevice(&out->device) == hipSuccess)
-    out->direct = std::move(rec.launches);
+  if (out && is_recorded(g, rec)) {
+    if (hipGetDevice(&out->device) == hipSuccess) out->direct = std::move(rec.launches);
+  }
   (void)hipGraphDestroy(g);
   if (e != hipSuccess) return DSV_ERR_HIP;
   if (!out) {
@@ -406,11 +414,16 @@ int dsv_graph_replay(void *graph_exec, void *hip_stream) {
   int dev = -1;
   if (!g->direct.empty() && hipGetDevice(&dev) == hipSuccess && dev == g->device &&
       not_capturing(s)) {
-    for (LaunchRecord r : g->direct)
+    for (const LaunchRecord &r : g->direct)
       if (launch_record(r, s) != hipSuccess) return DSV_ERR_HIP;
     return DSV_OK;
   }
   return hipGraphLaunch(g->exec, s) == hipSuccess ? DSV_OK : DSV_ERR_HIP;
+}
+
+int dsv_graph_direct_launches(const void *graph_exec) {
+  if (!graph_exec) return DSV_ERR_NULL;
+  return (int)((const Graph *)graph_exec)->direct.size();
 }
 
 int dsv_graph_destroy(void *graph_exec) {

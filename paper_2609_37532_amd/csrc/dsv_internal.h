@@ -145,7 +145,7 @@ struct LaunchRecord {
 };
 // Launches r on s; notes it too if this thread is capturing s through
 // dsv_graph_capture_begin.
-hipError_t enqueue(LaunchRecord &r, hipStream_t s);
+hipError_t enqueue(const LaunchRecord &r, hipStream_t s);
 
 template <typename P>
 inline void pack_arg(LaunchRecord &r, size_t &used, P value) {

@@ -163,6 +163,7 @@ def test_validate_and_graph_and_timing_argument_errors():
     assert lib.dsv_validate_metadata(fake, fake, fake, ctypes.byref(bad), fake, None) == -3
     assert lib.dsv_graph_capture_begin(None) == -1
     assert lib.dsv_graph_replay(None, None) == -1
+    assert lib.dsv_graph_direct_launches(None) == -1
     assert lib.dsv_graph_destroy(None) == -1
     assert lib.dsv_timing_start(0) == -2
     assert lib.dsv_timing_stop(None, None) == -1

@@ -1,7 +1,7 @@
 """Replays of every form of captured graph: a few launches of the library
-(replayed as launches), many of them, and launches mixed with another
-library's kernel (replayed as a graph).  Every replay, with changed inputs and
-other work between, equals the eager result."""
+(replayed as those launches), many, and launches mixed with another library's
+kernel or made on a second stream (replayed as a graph).  Every replay, with
+changed inputs and other work between, equals the eager result."""
 import numpy as np
 import pytest
 
@@ -13,7 +13,7 @@ try:
     import torch
 
     import paper_2609_37532_amd as dsv
-    from gpu_util import DEV, AcceptDev
+    from gpu_util import DEV, AcceptDev, DvlDev
 except Exception:  # pragma: no cover
     pass
 
@@ -25,9 +25,20 @@ def inputs(seed):
                                 dtype="bf16")
 
 
-@pytest.mark.parametrize("calls,foreign", [(1, False), (8, False), (9, False), (2, True)])
+def direct(g):
+    """The launches a replay of g makes in place of the graph."""
+    return dsv.load().dsv_graph_direct_launches(g._exec)
+
+
+def few(launches):
+    """What direct() is for a few launches of the library alone."""
+    return launches
+
+
+@pytest.mark.parametrize("calls,foreign", [(1, False), (3, False), (4, False), (8, False),
+                                           (9, False), (2, True)])
 def test_replays_equal_eager(calls, foreign):
-    # calls of accept are two launches each: 2, 16 and 18 launches
+    # calls of accept are two launches each
     d, other = AcceptDev(inputs(calls)), AcceptDev(inputs(100 + calls))
     stream = torch.cuda.Stream()
     count = torch.zeros(1, dtype=torch.int32, device=DEV)
@@ -45,6 +56,7 @@ def test_replays_equal_eager(calls, foreign):
     g = dsv.Graph().capture(work, stream)
     torch.cuda.synchronize()
     assert int(count) == 0  # captured, not run
+    assert direct(g) == (few(2 * calls) if calls <= 3 and not foreign else 0)
     for step in range(4):
         new = AcceptDev(inputs(1000 * calls + step))
         new.run()
@@ -84,3 +96,55 @@ def test_replay_on_another_stream_and_two_captures_at_once():
         assert np.array_equal(ga, a) and np.array_equal(gn, n)
     g1.close()
     g2.close()
+
+
+def dvl_inputs(seed):
+    return W.make_dvl_inputs(np.random.default_rng(seed), n_bs=70, n_live=61 - seed % 7)
+
+
+def dvl_result(d):
+    return np.concatenate([v.view(np.int32).ravel() for v in d.result().values()])
+
+
+@pytest.mark.parametrize("form", ["one", "two", "foreign", "side stream", "both streams"])
+def test_what_is_replayed_as_launches(form):
+    d = DvlDev(dvl_inputs(0))
+    stream, side, third = (torch.cuda.Stream() for _ in range(3))
+    count = torch.zeros(1, dtype=torch.int32, device=DEV)
+
+    def work():
+        if "stream" in form:  # forked off the captured stream, and joined again
+            side.wait_stream(stream)
+            d.run(stream=side)
+            stream.wait_stream(side)
+        if form != "side stream":
+            d.run(stream=stream)
+        if form == "two":
+            d.run(stream=stream)
+        if form == "foreign":
+            with torch.cuda.stream(stream):
+                count.add_(1)
+
+    work()
+    torch.cuda.synchronize()
+    g = dsv.Graph().capture(work, stream)
+    assert direct(g) == {"one": 1, "two": few(2)}.get(form, 0)
+    null = torch.cuda.default_stream()
+    for step, on in enumerate([stream, third, "captured", null, stream]):
+        new = DvlDev(dvl_inputs(1 + step))
+        new.run()
+        for name in ("logits", "num_live", "tokens", "positions", "kv_refs"):
+            getattr(d, name).copy_(getattr(new, name))
+        for out in (d.k, d.cu, d.ptok, d.ppos, d.pref, d.scores):
+            out.fill_(DvlDev.POISON)
+        torch.cuda.synchronize()
+        if on == "captured":
+            # into a stream that is being captured: run at once or with the
+            # graph that is captured, as the runtime has it, but always run
+            outer = dsv.Graph().capture(lambda: g.replay(third), third)
+            assert direct(outer) == 0
+            outer.replay(third)
+        else:
+            g.replay(on)
+        assert np.array_equal(dvl_result(d), dvl_result(new)), (form, step)
+    g.close()
