@@ -397,10 +397,15 @@ int dsv_dvl_allocate_pack(const float *pred_logits, const int32_t *num_live,
  *  dsv_graph_capture_end    ends capture and instantiates; *graph_exec
  *                           receives an opaque handle owned by the caller
  *                           (NULL on failure).
- *  dsv_graph_replay         enqueues one replay on `hip_stream`.  A graph of at
- *                           most six of the library's launches and nothing else
- *                           is replayed as those launches.  After DSV_ERR_HIP a
- *                           part of the replay may have been enqueued.
+ *  dsv_graph_replay         enqueues one replay on `hip_stream`.  Launches and
+ *                           replays that other threads make on the stream
+ *                           through this library come before or after the
+ *                           whole replay.  So does other work, if the HIP
+ *                           runtime keeps a graph launch together (7.2 does, 7.0
+ *                           does not).  A graph of at most six of the library's
+ *                           launches and nothing else may be replayed as those
+ *                           launches.  After DSV_ERR_HIP a part of the replay
+ *                           may have been enqueued.
  *  dsv_graph_direct_launches
  *                           the launches that a replay makes in place of the
  *                           graph, 0 if it launches the graph (for tests).

@@ -1,7 +1,11 @@
-"""Replays of every form of captured graph: a few launches of the library
-(replayed as those launches), many, and launches mixed with another library's
-kernel or made on a second stream (replayed as a graph).  Every replay, with
-changed inputs and other work between, equals the eager result."""
+"""Replays of every form of captured graph: one launch of the library (replayed
+as that launch), a few (replayed as launches where the HIP runtime does not keep
+a graph together either), many, and launches mixed with another library's kernel
+or made on a second stream (replayed as a graph).  Every replay, with changed inputs
+and other work between, equals the eager result, and is one operation to other
+threads' calls on its stream."""
+import threading
+
 import numpy as np
 import pytest
 
@@ -32,7 +36,8 @@ def direct(g):
 
 def few(launches):
     """What direct() is for a few launches of the library alone."""
-    return launches
+    major, minor = (int(x) for x in torch.version.hip.split(".")[:2])
+    return launches if (major, minor) < (7, 1) else 0
 
 
 @pytest.mark.parametrize("calls,foreign", [(1, False), (3, False), (4, False), (8, False),
@@ -148,3 +153,98 @@ def test_what_is_replayed_as_launches(form):
             g.replay(on)
         assert np.array_equal(dvl_result(d), dvl_result(new)), (form, step)
     g.close()
+
+
+def beside(work):
+    """Runs work(stopped) in a thread; leaving the context ends and joins it."""
+    class Beside:
+        def __enter__(self):
+            self.stop = threading.Event()
+            self.error = None
+            self.thread = threading.Thread(target=self.run)
+            self.thread.start()
+
+        def run(self):
+            try:
+                work(self.stop.is_set)
+            except Exception as e:  # reported by the test's thread
+                self.error = e
+
+        def __exit__(self, *exc):
+            self.stop.set()
+            self.thread.join()
+            assert self.error is None, self.error
+            return False
+
+    return Beside()
+
+
+@pytest.mark.parametrize("calls", [1, 6, 18])
+def test_no_call_of_another_thread_comes_inside_a_replay(calls):
+    # calls that read one input, which another thread's calls overwrite on the
+    # same stream: within a replay all of them saw the same value
+    n_bs, w = 8, 16
+    d = DvlDev(W.make_dvl_inputs(np.random.default_rng(3), n_bs=n_bs, n_live=n_bs))
+    ones = [torch.full_like(d.tokens, v) for v in (1, 2)]
+    half = d.tokens.view(-1)[:w * n_bs // 2]  # written by the other thread's packing
+    stream, steps = torch.cuda.Stream(), 400
+    outs = lambda: [torch.zeros_like(x) for x in (d.k, d.cu, d.ppos, d.pref)]  # noqa: E731
+    mine, theirs = outs(), outs()
+    packed = torch.zeros((calls, d.ptok.numel()), dtype=torch.int32, device=DEV)
+    seen = torch.zeros((steps, *packed.shape), dtype=torch.int32, device=DEV)
+
+    def pack(tokens, into, o):
+        dsv.dvl_allocate_pack(d.logits, d.num_live, tokens, d.positions, d.kv_refs, o[0], o[1],
+                              into, o[2], o[3], stream=stream)
+
+    def overwrite(stopped):
+        for n in range(100_000):
+            if stopped():
+                break
+            pack(ones[n % 2], half, theirs)
+
+    d.tokens.fill_(1)
+    torch.cuda.synchronize()
+    g = dsv.Graph().capture(lambda: [pack(d.tokens, out, mine) for out in packed], stream)
+    assert direct(g) == {1: 1, 6: few(6), 18: 0}[calls]
+    with beside(overwrite):
+        for step in range(steps):
+            g.replay(stream)
+            with torch.cuda.stream(stream):
+                seen[step].copy_(packed)
+    torch.cuda.synchronize()
+    g.close()
+    rows = seen.cpu().numpy()
+    assert np.unique(rows[:, 0, 0]).size == 2  # the other thread's calls were there
+    torn = [step for step in range(steps) if (rows[step] != rows[step, 0]).any()]
+    assert not torn, (len(torn), rows[torn[0]][:, 0])
+
+
+def test_two_threads_replay_graphs_that_share_a_stream_and_a_workspace():
+    x, y = AcceptDev(inputs(11)), AcceptDev(inputs(12))
+    y.ws = x.ws
+    want = []
+    for d in (x, y):
+        d.run()
+        want.append(np.stack(d.result()))
+    assert not np.array_equal(want[0], want[1])
+    stream = torch.cuda.Stream()
+    graphs = [dsv.Graph().capture(lambda d=d: d.run(stream=stream), stream) for d in (x, y)]
+    steps = 300
+    seen = torch.zeros((2, steps, 2, want[0].shape[1]), dtype=torch.int32, device=DEV)
+    torch.cuda.synchronize()
+
+    def replays(n, d):
+        for step in range(steps):
+            graphs[n].replay(stream)
+            with torch.cuda.stream(stream):
+                seen[n, step, 0].copy_(d.a)
+                seen[n, step, 1].copy_(d.nxt)
+
+    with beside(lambda stopped: replays(1, y)):
+        replays(0, x)
+    torch.cuda.synchronize()
+    got = seen.cpu().numpy()
+    for n in range(2):
+        assert (got[n] == want[n][None]).all(), n
+        graphs[n].close()
