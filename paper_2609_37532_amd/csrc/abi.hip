@@ -198,6 +198,17 @@ bool not_capturing(hipStream_t s) {
   return cs == hipStreamCaptureStatusNone;
 }
 
+// Device of stream s, -1 if that is not the current one or a query fails.
+int device_of(hipStream_t s) {
+  int dev = -1;
+  hipDevice_t of_stream = -1;
+  if (hipGetDevice(&dev) != hipSuccess || hipStreamGetDevice(s, &of_stream) != hipSuccess) {
+    (void)hipGetLastError();
+    return -1;
+  }
+  return of_stream == dev ? dev : -1;
+}
+
 // Whether graph g is exactly the recorded launches: as many nodes, all of them
 // kernels (each recorded launch made one).  They were made on one stream, so
 // they run in order.
@@ -455,7 +466,8 @@ int dsv_graph_capture_end(void *hip_stream, void **graph_exec) {
   const hipError_t e = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
   Graph *out = e == hipSuccess ? new (std::nothrow) Graph{ex, -1, {}} : nullptr;
   if (out && is_recorded(g, rec) && (rec.launches.size() == 1 || runtime_splits_graphs())) {
-    if (hipGetDevice(&out->device) == hipSuccess) out->direct = std::move(rec.launches);
+    out->device = device_of((hipStream_t)hip_stream);
+    if (out->device >= 0) out->direct = std::move(rec.launches);
   }
   (void)hipGraphDestroy(g);
   if (e != hipSuccess) return DSV_ERR_HIP;
@@ -472,11 +484,9 @@ int dsv_graph_replay(void *graph_exec, void *hip_stream) {
   const Graph *g = (const Graph *)graph_exec;
   const hipStream_t s = (hipStream_t)hip_stream;
   StreamTurn turn(s);
-  // launches go to the current device, and a stream that is itself being
-  // captured is given the graph
-  int dev = -1;
-  if (!g->direct.empty() && hipGetDevice(&dev) == hipSuccess && dev == g->device &&
-      not_capturing(s)) {
+  // another device, or a stream that is itself being captured, is given the
+  // graph
+  if (!g->direct.empty() && device_of(s) == g->device && not_capturing(s)) {
     for (const LaunchRecord &r : g->direct)
       if (launch_record(r, s) != hipSuccess) return DSV_ERR_HIP;
     return DSV_OK;
