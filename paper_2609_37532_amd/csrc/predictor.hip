@@ -7,8 +7,7 @@
 //
 // How: the first layer is a small GEMM, [N x in_dim] x [in_dim x 64], split
 // over K so that each workgroup reads its slice of W1 once for a tile of 16,
-// 32 or 64 requests (the smallest that leaves every workgroup resident): the
-// W1 slice and the feature tile go to LDS, and each thread accumulates one
+// 32 or 64 requests (by the rule at tile_rows): the W1 slice and the feature tile go to LDS, and each thread accumulates one
 // hidden unit for a quarter of the tile's requests, reading features as
 // LDS broadcasts.  Partial sums go to a workspace in
 // slice order; a second kernel, one wave per request, adds them in that
@@ -26,18 +25,19 @@ constexpr int kThreads = 256;
 constexpr int kRowGroups = kThreads / kH;  // 4: one per wave
 constexpr int kLdsStride = kKT + 4;        // keeps float4 rows aligned
 
-// Requests per tile: the smallest of 16, 32 and 64 that keeps the first kernel
-// at no more than kMaxTiles workgroups (two to a CU, all resident at once).
-// Smaller tiles spread the products over more CUs, and reread the W1 slices
-// from L2; a row's arithmetic is the same in every tile.  With 1,735 features,
-// predictor + DVL, tiles of 16 / 32 / 64 requests: 32 requests 17.7 / 20.0 /
-// - us, 64: 14.9 / - / 18.7, 128: 21.9 / - / 25.4, 256: 23.3 / - / 24.1, 512:
-// 35.9 / - / 32.7.
+// Requests per tile: 16 while that keeps the first kernel at no more than
+// kMaxTiles workgroups, two to each of 256 CUs; past it 64, or 32 where that holds
+// the bucket and there are few slices.  Smaller tiles spread the products over
+// more CUs and reread the W1 slices from L2; a row's arithmetic is the same in
+// every tile.  us a call (both kernels, 1,735 features, 28 slices), tiles of 16 /
+// 64: 33 requests 7.3 / 10.9, 128 (224 workgroups of 16) 7.5 / 11.0, 160 (280) 10.0
+// / 10.9, 288 (504) 10.5 / 11.4; 289 (532) 12.2 / 11.4, 384 13.3 / 11.7, 1024 25.6 /
+// 15.6.  Tiles of 32, 289 / 384 / 512 requests: 12.8 / 15.1 / 15.4.  32 requests,
+// tiles of 32 / 64: 70,000 features (1,094 slices) 77.1 / 68.3.
 constexpr int kMaxTiles = 512;
 int tile_rows(int n_bs, int slices) {
-  int rows = 16;
-  while (rows < 64 && (long long)slices * ((n_bs + rows - 1) / rows) > kMaxTiles) rows *= 2;
-  return rows;
+  if (n_bs <= 16 || (long long)slices * ((n_bs + 15) / 16) <= kMaxTiles) return 16;
+  return n_bs <= 32 && slices <= kMaxTiles ? 32 : 64;
 }
 
 __device__ __forceinline__ int live_count(const int32_t *num_live, int n_bs) {

@@ -95,6 +95,15 @@ def test_parity_other_shapes(dims):
     check(d, "dims %s" % (dims,))
 
 
+@pytest.mark.parametrize("n_bs,in_dim", [(16, 33000), (17, 33000), (20, 20000), (288, 1735),
+                                         (289, 1735), (512, 1735)])
+def test_parity_at_the_tile_rule(n_bs, in_dim):
+    # tiles of 16, 64, 32, 16, 64 and 64 requests
+    d = W.make_predictor_inputs(np.random.default_rng(9300 + n_bs), n_bs=n_bs, n_live=n_bs - 1,
+                                dims=(in_dim, 64, 15))
+    check(d, "tiles %d %d" % (n_bs, in_dim))
+
+
 def test_deterministic_and_clamped():
     d = W.make_predictor_inputs(np.random.default_rng(9200), n_bs=48, n_live=48)
     got, dev = check(d, "base")
