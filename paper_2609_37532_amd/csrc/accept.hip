@@ -94,6 +94,24 @@ __device__ __forceinline__ void take_vec(u32x4 x, int base, float &bv, int &bi) 
   }
 }
 
+// A thread's best over its kUnroll vectors of a chunk, every load in flight at
+// once.  A chunk that is short of vectors (not kFull: its row starts off 16 bytes,
+// or it is the row's last) clamps the index and takes some twice, which changes
+// nothing.
+template <bool kBf16, int kUnroll, bool kFull>
+__device__ __forceinline__ void take_vecs(const u32x4 *vp, int nvec, int vb, float &bv, int &bi) {
+  constexpr int kVec = kBf16 ? 8 : 4;
+  const int tid = threadIdx.x;
+  auto at = [&](int u) {
+    return kFull ? u * kThreads + tid : min(u * kThreads + tid, nvec - 1);
+  };
+  u32x4 x[kUnroll];
+#pragma unroll
+  for (int u = 0; u < kUnroll; ++u) x[u] = __builtin_nontemporal_load(vp + at(u));
+#pragma unroll
+  for (int u = 0; u < kUnroll; ++u) take_vec<kBf16>(x[u], vb + at(u) * kVec, bv, bi);
+}
+
 template <bool kBf16>
 __global__ __launch_bounds__(kThreads) void argmax_chunk_kernel(
     const void *logits, const int32_t *cu, int32_t num_reqs, int32_t cap,
@@ -121,20 +139,17 @@ __global__ __launch_bounds__(kThreads) void argmax_chunk_kernel(
   if (tid < head) take(bv, bi, elem<kBf16>(row, begin + tid), begin + tid);
   if (tid < end - ve) take(bv, bi, elem<kBf16>(row, ve + tid), ve + tid);
   const u32x4 *vp = (const u32x4 *)(row + (size_t)vb * kEs);
-  // Every load of the chunk in flight at once.  A chunk that is short of
-  // vectors (its row starts off 16 bytes, or it is the row's last) clamps the
-  // index and takes some twice, which changes nothing; a loop over the vectors
-  // it has waited for each load in turn (fp32, 50,257 tokens, 238 rows: 12.1
-  // us, now 10.8).
-  if (nvec > 0) {
-    u32x4 x[kUnroll];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u)
-      x[u] = __builtin_nontemporal_load(vp + min(u * kThreads + tid, nvec - 1));
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u)
-      take_vec<kBf16>(x[u], vb + min(u * kThreads + tid, nvec - 1) * kVec, bv, bi);
-  }
+  // Short chunks of at most two rounds take a loop, which waits for each load but
+  // makes no others (us a call, fp32, one row, in the loop / all at once: 500
+  // tokens 5.37 / 5.85, 2,000 tokens 5.65 / 5.92, 8,000 tokens 6.88 / 5.98; 238
+  // rows of 50,257 tokens 13.3 / 11.2).
+  if (nvec == kThreads * kUnroll)
+    take_vecs<kBf16, kUnroll, true>(vp, nvec, vb, bv, bi);
+  else if (nvec > 2 * kThreads)
+    take_vecs<kBf16, kUnroll, false>(vp, nvec, vb, bv, bi);
+  else
+    for (int q = tid; q < nvec; q += kThreads)
+      take_vec<kBf16>(__builtin_nontemporal_load(vp + q), vb + q * kVec, bv, bi);
 
   // wave reduction (the result lands in lane 63), then across the four
   // waves through LDS

@@ -118,6 +118,51 @@ __device__ __forceinline__ void wave_merge(float &m, float &s) {
   dpp_merge<0x143, 0xc>(m, s);
 }
 
+// (max, sum) of a thread's kLoads vectors of a chunk's nvec, every load in flight
+// at once and the values kept in registers: their maximum first and then one
+// exponential each.  Vectors past the chunk's last (its row starts off 16 bytes,
+// or it is the row's last chunk) read the last again and count as -inf.
+template <bool kBf16, int kLoads>
+__device__ __forceinline__ void acc_vecs(const u32x4 *vp, int nvec, float c, float &m, float &s) {
+  constexpr int kVec = kBf16 ? 8 : 4;
+  constexpr int kN = kLoads * kVec;
+  const int tid = threadIdx.x;
+  u32x4 x[kLoads];
+#pragma unroll
+  for (int u = 0; u < kLoads; ++u)
+    x[u] = __builtin_nontemporal_load(vp + min(u * kThreads + tid, nvec - 1));
+  float y[kN];
+#pragma unroll
+  for (int u = 0; u < kLoads; ++u) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (kBf16) {
+        y[u * kVec + 2 * q] = scaled(bf16_lo(x[u][q]), c);
+        y[u * kVec + 2 * q + 1] = scaled(bf16_hi(x[u][q]), c);
+      } else {
+        y[u * kVec + q] = scaled(__uint_as_float(x[u][q]), c);
+      }
+    }
+  }
+  if (nvec < kThreads * kLoads) {
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u)
+      if (u * kThreads + tid >= nvec) {
+#pragma unroll
+        for (int q = 0; q < kVec; ++q) y[u * kVec + q] = -INFINITY;
+      }
+  }
+  float lm = y[0];
+#pragma unroll
+  for (int q = 1; q < kN; ++q) lm = fmaxf(lm, y[q]);
+  float ls = 0.f;
+  if (lm > -INFINITY) {
+#pragma unroll
+    for (int q = 0; q < kN; ++q) ls += fexp2(y[q] - lm);
+  }
+  merge(m, s, lm, ls);
+}
+
 // Per (chunk, live row): max of logits * c and sum of exp2(logits * c - max).
 template <bool kBf16>
 __global__ __launch_bounds__(kThreads) void softmax_stats_kernel(
@@ -142,47 +187,12 @@ __global__ __launch_bounds__(kThreads) void softmax_stats_kernel(
   if (tid < head) acc(m, s, scaled(elem<kBf16>(row, begin + tid), c));
   if (tid < end - ve) acc(m, s, scaled(elem<kBf16>(row, ve + tid), c));
   const u32x4 *vp = (const u32x4 *)(row + (size_t)vb * kEs);
-  if (nvec > 0) {
-    // Every load of the chunk in flight at once, the values kept in registers:
-    // their maximum first and then one exponential each.  Vectors past the
-    // chunk's last (its row starts off 16 bytes, or it is the row's last
-    // chunk) read the last again and count as -inf.
-    constexpr int kN = kUnroll * kVec;
-    u32x4 x[kUnroll];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u)
-      x[u] = __builtin_nontemporal_load(vp + min(u * kThreads + tid, nvec - 1));
-    float y[kN];
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (kBf16) {
-          y[u * kVec + 2 * q] = scaled(bf16_lo(x[u][q]), c);
-          y[u * kVec + 2 * q + 1] = scaled(bf16_hi(x[u][q]), c);
-        } else {
-          y[u * kVec + q] = scaled(__uint_as_float(x[u][q]), c);
-        }
-      }
-    }
-    if (nvec < kThreads * kUnroll) {
-#pragma unroll
-      for (int u = 0; u < kUnroll; ++u)
-        if (u * kThreads + tid >= nvec) {
-#pragma unroll
-          for (int q = 0; q < kVec; ++q) y[u * kVec + q] = -INFINITY;
-        }
-    }
-    float lm = y[0];
-#pragma unroll
-    for (int q = 1; q < kN; ++q) lm = fmaxf(lm, y[q]);
-    float ls = 0.f;
-    if (lm > -INFINITY) {
-#pragma unroll
-      for (int q = 0; q < kN; ++q) ls += fexp2(y[q] - lm);
-    }
-    merge(m, s, lm, ls);
-  }
+  // a short chunk, of at most two rounds, without the rest of the loads (us a call,
+  // fp32, one request, two rounds / all: 1,000 tokens 8.65 / 9.13, 2,000 8.61 / 9.16)
+  if (nvec > 2 * kThreads)
+    acc_vecs<kBf16, kUnroll>(vp, nvec, c, m, s);
+  else if (nvec > 0)
+    acc_vecs<kBf16, 2>(vp, nvec, c, m, s);
   wave_merge(m, s);  // complete in lane 63
   __shared__ float sm[kThreads / kWave], ss[kThreads / kWave];
   const int wave = tid / kWave, lane = tid % kWave;

@@ -58,6 +58,20 @@ def test_vocab_sizes_and_alignment(dtype, vocab):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rounds", [1, 2, 3])
+@pytest.mark.parametrize("more", [-1, 0, 1])
+def test_chunks_of_whole_rounds(dtype, rounds, more):
+    # chunks at the edges of 256-thread rounds of 16-byte loads, and one token
+    # to either side, alone and after a full chunk of 8,192
+    rng = np.random.default_rng(rounds)
+    for full in (0, 8192):
+        vocab = full + rounds * 256 * (4 if dtype == "f32" else 8) + more
+        acc = W.make_accept_inputs(rng, cu_qlens=W.cu_from_lengths([1, 16, 5, 0, 3]), capacity=30,
+                                   vocab=vocab, dtype=dtype, p_accept=0.4)
+        check(acc, "rounds vocab%d-%s" % (vocab, dtype))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_ties_across_chunks_and_lanes(dtype):
     rng = np.random.default_rng(4)
     vocab = 3 * 8192 + 100

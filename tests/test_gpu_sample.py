@@ -113,6 +113,17 @@ def test_parity(dtype, V, B, T, seed):
     compare(ga, gt, logits, dtype, cu, draft, U, T, "%s V=%d B=%d T=%g" % (dtype, V, B, T))
 
 
+@pytest.mark.parametrize("dtype,V", [("f32", 2047), ("f32", 2048), ("f32", 2053), ("f32", 10240),
+                                     ("bf16", 4095), ("bf16", 4096), ("bf16", 4105),
+                                     ("bf16", 12288)])
+def test_parity_at_the_short_chunk_rule(dtype, V):
+    # chunks of two 256-thread rounds of 16-byte loads, and to either side
+    rng = np.random.default_rng(8050 + V)
+    logits, cu, draft, U = make_case(rng, 8, V, dtype)
+    ga, gt = run_gpu(logits, dtype, cu, draft, U, 0.9)
+    compare(ga, gt, logits, dtype, cu, draft, U, 0.9, "%s V=%d" % (dtype, V))
+
+
 def test_first_emitted_token_follows_target():
     rng = np.random.default_rng(8100)
     V, k, n, T = 12, 4, 16000, 0.9  # capacity n*k stays within 65535 rows
