@@ -46,18 +46,19 @@
 //    factor 2^8, which keeps the weights below 2^8.  It is kept an integer,
 //    so rescales and merge weights are exact powers of two.
 //  * Waves of a workgroup split the dims when a request has one or two row
-//    tiles; beyond that each wave owns one or two tiles, so that every piece
+//    tiles; beyond that each wave owns one to four tiles, so that every piece
 //    reads its K and V once: four waves hold the eight tiles of eight query
-//    heads to a KV head and a full block, eight waves the sixteen of G = 16.
-//  * The workgroup placed second on a CU runs at raised wave priority over
-//    half of its share, so that both workgroups of a CU finish together.
+//    heads to a KV head and a full block, and at D = 64 the sixteen of G = 16,
+//    which eight waves hold at D = 128.
+//  * The workgroups placed after the first on a CU run at raised wave priority
+//    over half of their share, so that a CU's workgroups finish together.
 //
 // What bounds it, and what it measured (MI355X, split + combine kernels, us a
 // call; before: each wave held one tile, so that more than four took a pass of
 // K and V for every four, and a step's softmax took 132 vector instructions to
 // a tile where it now takes about 60):
-//   B=32, 32 query / 8 KV heads, contexts to 8K (0.6 GB): HBM; 105.7 -> 104.1,
-//     5.8 TB/s
+//   B=32, 32 query / 8 KV heads, contexts to 8K (0.6 GB): HBM; 105.7 -> 104.1
+//     (less than single runs differ by), 5.8 TB/s
 //   B=32, 64 / 8 heads, lengths about 8, contexts to 16K (1.2 GB): HBM, with
 //     the vector units close behind; 343 -> 228, 5.3 TB/s
 //   B=24, 32 / 2 heads, full blocks, contexts to 6K: the matrix and vector
@@ -89,15 +90,19 @@ constexpr int kMinShare = 8 * kBlockKeys;
 // shares are equal in streaming plus piece starts.  A multiple of the block;
 // six blocks measured best across shapes (two to eight were compared).
 constexpr int kLeadKeys = kAttnLeadKeys;
-// Wave priority.  The persistent grid holds two workgroups per CU, and the
-// one the dispatcher places second (grid index >= number of CUs) loses
-// instruction arbitration to the older first one: with equal shares and no
-// priorities the first ended at 66 us and the second at 91 (B=32, contexts up
-// to 8K).  Its waves therefore run at raised priority until kBoostPct percent
-// of its share is done, then at the default, and both end at about 90 us.
+// Wave priority.  At D = 128 the persistent grid holds two workgroups per CU
+// (one at G = 16), and the one the dispatcher places second (grid index >= number
+// of CUs) loses instruction arbitration to the older first one: with equal
+// shares and no priorities the first ended at 66 us and the second at 91 (B=32,
+// contexts up to 8K).  Its waves therefore run at raised priority until kBoostPct
+// percent of its share is done, then at the default, and both end at about 90 us.
 // Priority changes no arithmetic.  Drop points, B=32 contexts to 8K / eight
 // query heads to a KV head and contexts to 16K, us a call: 50% 104.2 / 226.7,
 // 65% 104.4 / 228.8, 80% 106.1 / 229.6, none 113 / 244.
+// At D = 64, with two to four workgroups to a CU, all but the first are raised: 8 KV
+// heads, B=32 contexts to 8K, groups of 1 / 4 / 8 / 16, us a call: 56.4 / 60.3 /
+// 66.3 / 108.4, none raised 57.7 / 61.9 / 70.1 / 116.1, the last alone 56.5 / 60.7 /
+// 68.3 / 108.9.
 constexpr int kBoostPct = 50;
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) {
@@ -932,16 +937,23 @@ __device__ __forceinline__ void run_piece(const AttnParams &p, char *buf, int *i
     write_rows<D, NE>(p, x, role.tile0 + t, role.e_lo, lane, st.m[t], row_sum4(st.l[t]), st.o[t]);
 }
 
-// NW waves: four, two workgroups to a CU; eight, one to a CU, for G = 16,
-// whose requests may have more than eight row tiles.  kTwo: requests may have
-// more than NW row tiles (G = 8 and 16), two to a wave.  At D = 64 a step is
-// half the bytes and a wave needs half the registers, so four workgroups fit a
-// CU (three with two tiles to a wave; four would spill): 16 requests of 10K
-// keys on one KV head take 22.5 us instead of 26.4, 33 short ones of eight
-// heads to a KV head 39.5 instead of 43.5.  At D = 128 three to a CU measured
-// slower (36 requests, contexts to 2K, four layers: 232.8 -> 252.9 us).
-template <int D, int NW, bool kTwo>
-__global__ __launch_bounds__(NW *kWave, D == 64 && NW == 4 ? (kTwo ? 3 : 4) : 2) void attn_streamk_kernel(AttnParams p) {
+// NW waves, each with up to kTW row tiles: as many as the group's largest
+// requests have (16 rows of each head).  Workgroups to a CU, by registers: two
+// of four waves at D = 128 (three measured slower: 36 requests, contexts to 2K,
+// four layers 232.8 -> 252.9 us) and one of eight (G = 16).  At D = 64 a step is half
+// the bytes and a wave needs half the registers: four workgroups with one tile to a
+// wave, three with two (four would spill): 16 requests of 10K keys on one KV head
+// take 22.5 us instead of 26.4, 33 short ones of eight heads to a KV head 39.5
+// instead of 43.5.  And two with four tiles (G = 16), where eight waves to a lone
+// workgroup keep few of them busy on short requests: 32 requests, contexts to 8K,
+// 16 heads on each of 8 KV heads, one row each 75.0 -> 64.4 us, lengths of a
+// geometric distribution 156.6 -> 107.0, full blocks 165 -> 150; 8 full blocks to
+// 2K lose 28.4 -> 30.5, 4 requests of 6 rows to 16K 34.8 -> 38.5.
+constexpr int min_waves_per_simd(int D, int NW, int kTW) {
+  return D == 64 && NW == 4 ? (kTW == 1 ? 4 : (kTW == 2 ? 3 : 2)) : 2;
+}
+template <int D, int NW, int kTW>
+__global__ __launch_bounds__(NW *kWave, min_waves_per_simd(D, NW, kTW)) void attn_streamk_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(1024))) char buf[Ring<D, NW>::kBytes];
   __shared__ int ids[kSubPages];
   __shared__ int lds_plan[2 * NW + 8 + (kNumPieceCaps / 2 + 2) * NW];
@@ -989,16 +1001,22 @@ __global__ __launch_bounds__(NW *kWave, D == 64 && NW == 4 ? (kTwo ? 3 : 4) : 2)
     // the piece forms ahead of the loop, and spills them
     asm volatile("" : "+v"(lane), "+s"(wave));
     const int nt = (p.group * x.rq.k + 15) / 16;  // row tiles
-    // one or two tiles split their dims over the waves (with eight waves, which
-    // serve G = 16, so short a request leaves the others idle)
+    // one or two tiles split their dims over four waves.  Eight waves don't split
+    // them: each would read all of K from LDS (D = 128, 32 requests, contexts to
+    // 8K, 8 KV heads, two rows each: 119.5 us, split 135.0).
     constexpr int kBlocks = D / 16;
     if (NW == 4 && nt == 1)
       run_piece<D, 1, kBlocks / 4, NW>(p, buf, ids, x, wave, lane);
     else if (NW == 4 && nt == 2)
       run_piece<D, 1, kBlocks / 2, NW>(p, buf, ids, x, wave, lane);
-    else if (!kTwo || nt <= NW)
+    else if (kTW == 1 || nt <= NW)
       run_piece<D, 1, kBlocks, NW>(p, buf, ids, x, wave, lane);
-    else if constexpr (kTwo)
+    else if constexpr (kTW == 4) {
+      if (nt <= 2 * NW)
+        run_piece<D, 2, kBlocks, NW>(p, buf, ids, x, wave, lane);
+      else
+        run_piece<D, 4, kBlocks, NW>(p, buf, ids, x, wave, lane);
+    } else if constexpr (kTW == 2)
       run_piece<D, 2, kBlocks, NW>(p, buf, ids, x, wave, lane);
 
     pos += take;
@@ -1164,14 +1182,15 @@ struct SplitKernel {
   int threads;
 };
 SplitKernel split_kernel(int head_dim, int group) {
-  if (group > 8)
-    return {head_dim == 128 ? attn_streamk_kernel<128, 8, true> : attn_streamk_kernel<64, 8, true>,
-            8 * kWave};
-  if (group > 4)
-    return {head_dim == 128 ? attn_streamk_kernel<128, 4, true> : attn_streamk_kernel<64, 4, true>,
-            4 * kWave};
-  return {head_dim == 128 ? attn_streamk_kernel<128, 4, false> : attn_streamk_kernel<64, 4, false>,
-          4 * kWave};
+  constexpr int k4 = 4 * kWave, k8 = 8 * kWave;
+  if (head_dim == 128) {
+    if (group > 8) return {attn_streamk_kernel<128, 8, 2>, k8};
+    if (group > 4) return {attn_streamk_kernel<128, 4, 2>, k4};
+    return {attn_streamk_kernel<128, 4, 1>, k4};
+  }
+  if (group > 8) return {attn_streamk_kernel<64, 4, 4>, k4};
+  if (group > 4) return {attn_streamk_kernel<64, 4, 2>, k4};
+  return {attn_streamk_kernel<64, 4, 1>, k4};
 }
 
 // Workgroups the GPU holds at once for the split kernel (cached per device
@@ -1195,9 +1214,9 @@ int resident_workgroups(int head_dim, int group) {
 }  // namespace
 
 // Upper bound of the persistent grid, known without a device: at most 1024
-// workgroups (a 256-CU MI355X holds 512 of this kernel at once, two per CU) and never
-// more than the 32-key blocks the largest batch could hold.  The workspace
-// is sized for it.
+// workgroups and never more than the 32-key blocks the largest batch could hold.
+// The workspace is sized for it.  A 256-CU MI355X holds at once, by head_dim and
+// group: 128, up to 8: 512; 128, 16: 256; 64, up to 4: 1024; 64, 8: 768; 64, 16: 512.
 int32_t attn_grid_cap(const dsv_attn_dims &d) {
   constexpr long long kMaxGrid = 1024;
   const long long blocks = (long long)d.num_reqs * d.num_kv_heads *

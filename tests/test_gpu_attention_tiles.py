@@ -1,7 +1,7 @@
 """GPU parity of dsv_verify_attn where its work forms meet: row-tile counts
 around the limits of the wave roles (one and two tiles split their dims over
-the waves, three and more have waves of their own, twice over beyond four, or
-beyond eight at G = 16), with key counts around the 32-key stages of the ring
+the waves, three and more have waves of their own, twice over beyond four, at
+G = 16 beyond eight or, at d = 64, four times over), with key counts around the 32-key stages of the ring
 and the 16-token pages.  The bar is the attention bar of gpu_util."""
 import numpy as np
 import pytest
@@ -40,6 +40,21 @@ def test_row_tiles(group, k, d):
     # 17 requests with k rows each: ceil(group * k / 16) row tiles
     check("G=%d k=%d d=%d" % (group, k, d), 100 * group + k, EDGES, [k] * len(EDGES),
           2 * group, 2, d)
+
+
+@pytest.mark.parametrize("k", [4, 5, 12, 13])
+@pytest.mark.parametrize("d", [64, 128])
+def test_row_tiles_of_sixteen_heads(k, d):
+    # four waves at d = 64: tiles of one, two and up to four to a wave
+    check("G=16 k=%d d=%d" % (k, d), 1700 + k, EDGES, [k] * len(EDGES), 32, 2, d)
+
+
+@pytest.mark.parametrize("group", [4, 8, 16])
+def test_mixed_tiles_in_one_share_of_head_dim_64(group):
+    rng = np.random.default_rng(64 + group)
+    qlens = [int(k) for k in rng.integers(1, 17, size=48)]
+    ctx = [int(c) for c in rng.integers(200, 2600, size=48)]
+    check("G=%d d=64 mixed" % group, 107 + group, ctx, qlens, 4 * group, 4, 64)
 
 
 @pytest.mark.parametrize("group", [8, 16])
