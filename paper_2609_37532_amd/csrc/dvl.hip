@@ -65,11 +65,12 @@ __device__ __forceinline__ float score_in_full(float x) {
 
 // The same binary32 value from about 25 double-precision instructions, where
 // the library's exponential and the division take more than twice as many.
-// For |x| <= 80 the quotient y here is within 3e-13 of the sigmoid's value
-// (the exponential's series ends 2.2e-13 short at |r| = ln 2 / 2; the
-// reciprocal's seed is good to 1.8e-7 and one Newton step squares that), and
-// score_in_full's is within a few 1e-16.  Rounding is monotone, so if both
-// ends of y (1 +- 1e-12) round to one binary32 value, that is its result too.
+// For |x| <= 80 the quotient y here is within 3.5e-13 of the sigmoid's value,
+// relative: the exponential's series ends 2.2e-13 short at |r| = ln 2 / 2, which is
+// 3.1e-13 of e^r at r = -ln 2 / 2; the reciprocal's seed is good to 1.8e-7, and one
+// Newton step leaves its square, 3e-14.  score_in_full's value is within a few
+// 1e-16.  Rounding is monotone, so if both ends of y (1 +- 1e-12) round to one
+// binary32 value, that is its result too; the margin is nearly three times the bound.
 // Otherwise (one logit in 30,000), and for x < -80 or NaN, `sure` is false.
 // Above 17.4 every score is 1, so x is cut off at 80.
 // Over all 2^32 inputs the sure ones have score_in_full's bits.  The scores

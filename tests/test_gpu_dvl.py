@@ -208,3 +208,45 @@ def test_scores_at_hard_logits(n_bs, w):
     # a request's running minimum would hide most values: descending rows
     d.pred_logits[...] = -np.sort(-rng.choice(pool, size=d.pred_logits.shape), axis=1)
     check(d, "hard logits")
+
+
+def narrow_scores(x):
+    """Scores of the logits x, one to a request (block width 2): GPU and oracle."""
+    n = 1024
+    x = np.concatenate([x, np.zeros(-x.size % n, np.float32)]).reshape(-1, n, 1)
+    dev_x = torch.from_numpy(x).to(DEV)
+    got = torch.zeros((len(x), n, 2), dtype=torch.float32, device=DEV)
+    i32 = lambda *shape: torch.zeros(shape, dtype=torch.int32, device=DEV)
+    live, block, k, cu = i32_dev([n]), i32(n, 2), i32(n), i32(n + 1)
+    packed = [i32(n) for _ in range(3)]
+    for a, b in zip(dev_x, got):
+        dsv.dvl_allocate_pack(a, live, block, block, block, k, cu, *packed, b)
+    zeros = np.zeros((n, 2), np.int32)
+    ref = [oracle.dvl_allocate_pack(a, n, zeros, zeros, zeros, 2)["q"] for a in x]
+    torch.cuda.synchronize()
+    return x, got.cpu().numpy(), np.stack(ref)
+
+
+def assert_same_scores(x, got, ref):
+    bad = np.argwhere(got.view(np.uint32) != ref.view(np.uint32))
+    assert bad.size == 0, [(float(x[i, j, 0]), got[i, j], ref[i, j]) for i, j, _ in bad[:5]]
+
+
+def test_scores_outside_the_short_sigmoids_margin():
+    # The short form decides a logit whose sigmoid lies further than 1e-12
+    # (relative) from a rounding boundary: those within ten times that, where
+    # a wrong coefficient or too small a margin would show first.
+    x = np.random.default_rng(12).uniform(-80, 17, size=1 << 22).astype(np.float32)
+    y = 1.0 / (1.0 + np.exp(-x.astype(np.float64)))
+    f = y.astype(np.float32)
+    gap = np.minimum(*(np.abs(y - (f.astype(np.float64) + np.nextafter(f, np.float32(to))) / 2)
+                       for to in (0, 2))) / y
+    near = x[(gap > 1e-12) & (gap < 1e-11)]
+    assert near.size > 500
+    assert_same_scores(*narrow_scores(near))
+
+
+def test_scores_over_all_exponents():
+    # every 4,099th of the 2^32 bit patterns, infinities and NaN among them
+    bits = np.arange(0, 1 << 32, 4099, dtype=np.uint64).astype(np.uint32)
+    assert_same_scores(*narrow_scores(bits.view(np.float32)))
