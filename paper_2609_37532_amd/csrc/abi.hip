@@ -86,12 +86,13 @@ thread_local std::vector<Recording> t_recordings;
 // / 15.0 and 18.9 / 29.4 / 3.0; greedy acceptance, two, 16.0 / 35.8 / 23.6 and
 // 10.4 / 21.0 / 5.2; acceptance of one request three times, six, 23.1 / 33.7 /
 // 20.1 and 19.3 / 28.1 / 13.2; attention of three short layers, six, 40.4 /
-// 51.7 / 15.3 and 36.5 / 47.0 / 12.6.  From eight on the launches cost the caller more
-// than the graph does, and short ones the GPU too: acceptance four times, eight,
-// 28.0 / 38.6 / 21.3 and 25.2 / 47.6 / 25.3; attention of four layers, eight,
-// 52.4 / 63.7 / 15.7 and 48.7 / 59.5 / 22.1; of eight, sixteen, 101.0 / 112.9 /
-// 17.9 and 98.8 / 109.9 / 42.4.  Longer graphs, and graphs that hold anything
-// else, are launched as graphs.
+// 51.7 / 15.3 and 36.5 / 47.0 / 12.6.  The eighth launch in a row costs the host
+// some 20 us, so that from eight on the caller pays more than for the graph, and
+// short kernels wait for it: acceptance four times, eight, 28.0 / 38.6 / 21.3 and
+// 25.2 / 47.6 / 25.3; attention of four layers, eight, one head over 20 keys 33.3 /
+// 45.4 / 26.8 and 34.0 / 63.1 / 35.1, 8 KV heads over 700 keys 52.4 / 63.7 / 15.7 and
+// 48.7 / 59.5 / 22.1.  The lengths that tell these apart are not known to the host.
+// Longer graphs, and graphs that hold anything else, are launched as graphs.
 constexpr size_t kMaxDirect = 6;
 struct Graph {
   hipGraphExec_t exec;
