@@ -1,8 +1,9 @@
 """Benchmark of the verify hot path on one MI355X.
 
-One step = one replay of a captured hipGraph holding the whole path on one
-batch: verify attention (stream-K kernel + combine kernel) for one attention
-layer, then greedy acceptance (argmax kernel + prefix kernel).  Workload:
+One step = one replay of a captured graph holding the whole path on one batch:
+verify attention (stream-K kernel + combine kernel) for one attention layer,
+then greedy acceptance (argmax kernel + prefix kernel).  dsv_graph_replay makes
+its four launches again, or launches the graph, as the HIP runtime has it.  Workload:
 Qwen3-8B attention shape at concurrency 32 -- B=32 requests, 32 query / 8 KV
 heads, head_dim 128, bf16 paged KV (page 16), contexts uniform in
 [1024, 8192], verify lengths 1..16 (anchor + truncated geometric, p=0.25)
@@ -390,7 +391,7 @@ def dvl_bench(launches=100, replays=10):
         nbytes = n_bs * (w - 1) * 4 + 3 * m_bs * 4 + 8 + (2 * n_bs + 1) * 4 + 3 * m_bs * 4
         res["dvl_algorithmic_bytes"] = nbytes
         out["n_bs_%d" % n_bs] = res
-    out["bound"] = "latency (one workgroup for DVL; K-split tiles for the predictor)"
+    out["bound"] = "latency (one workgroup per 512 packed rows for DVL; K-split tiles for the predictor)"
     out["timing"] = "%d launches in one hipGraph, %d replays, HIP events" % (launches, replays)
     return out
 
@@ -658,7 +659,8 @@ def main():
     step_on(stream)  # eager run once before capture
     torch.cuda.synchronize()
     graph = dsv.Graph().capture(lambda: step_on(stream), stream)
-    log("graph captured")
+    form = "made as its launches" if graph.direct_launches() else "a graph launch"
+    log("graph captured; a replay is", form)
 
     # ---- timed region: K graph replays of the whole step
     with torch.cuda.stream(stream):
@@ -723,12 +725,13 @@ def main():
             "packed_tokens": tokens,
             "kv_tokens": int((attn.ctx_lens + attn.qlens).sum()),
             "capacity": attn.capacity,
-            "step": "one hipGraph replay: attn stream-K + combine + argmax + prefix",
+            "step": "one replay of the captured graph (%s): attn stream-K + combine + argmax + prefix"
+                    % form,
             "row_padding_eq2": row_padding(attn.qlens, hq // hkv),
         },
         "roofline": {
             "bound": "hbm",
-            "kernel": "attn_streamk_kernel<128>",
+            "kernel": "attn_streamk_kernel<128, 4, 1>",
             "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBPS,
             "unit": "GB/s",
@@ -755,7 +758,7 @@ def main():
                            "algorithmic_bytes": b_acc,
                            "gbps": round(b_acc / (t_argmax + t_prefix) / 1e9, 1),
                            "frac": round(b_acc / (t_argmax + t_prefix) / 1e9 / HBM_PEAK_GBPS, 4)},
-            "step": {"what": "one graph replay of all four kernels (ms_per_step)",
+            "step": {"what": "one replay of all four kernels (ms_per_step)",
                      "us": round(ms_step * 1e3, 2), "algorithmic_bytes": b_attn + b_acc,
                      "gbps": round((b_attn + b_acc) / (ms_step * 1e-3) / 1e9, 1),
                      "frac": round((b_attn + b_acc) / (ms_step * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4)},

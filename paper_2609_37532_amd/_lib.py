@@ -384,6 +384,12 @@ class Graph:
     def replay(self, stream) -> None:
         _check("dsv_graph_replay", load().dsv_graph_replay(self._exec, _stream_handle(stream)))
 
+    def direct_launches(self) -> int:
+        """Launches that a replay makes in place of the graph (0: it launches the graph)."""
+        n = load().dsv_graph_direct_launches(self._exec)
+        _check("dsv_graph_direct_launches", min(n, 0))
+        return n
+
     def close(self) -> None:
         if self._exec.value:
             load().dsv_graph_destroy(self._exec)

@@ -29,13 +29,8 @@ def inputs(seed):
                                 dtype="bf16")
 
 
-def direct(g):
-    """The launches a replay of g makes in place of the graph."""
-    return dsv.load().dsv_graph_direct_launches(g._exec)
-
-
 def few(launches):
-    """What direct() is for a few launches of the library alone."""
+    """What direct_launches() is for a few launches of the library alone."""
     major, minor = (int(x) for x in torch.version.hip.split(".")[:2])
     return launches if (major, minor) < (7, 1) else 0
 
@@ -61,7 +56,7 @@ def test_replays_equal_eager(calls, foreign):
     g = dsv.Graph().capture(work, stream)
     torch.cuda.synchronize()
     assert int(count) == 0  # captured, not run
-    assert direct(g) == (few(2 * calls) if calls <= 3 and not foreign else 0)
+    assert g.direct_launches() == (few(2 * calls) if calls <= 3 and not foreign else 0)
     for step in range(4):
         new = AcceptDev(inputs(1000 * calls + step))
         new.run()
@@ -133,7 +128,7 @@ def test_what_is_replayed_as_launches(form):
     work()
     torch.cuda.synchronize()
     g = dsv.Graph().capture(work, stream)
-    assert direct(g) == {"one": 1, "two": few(2)}.get(form, 0)
+    assert g.direct_launches() == {"one": 1, "two": few(2)}.get(form, 0)
     null = torch.cuda.default_stream()
     for step, on in enumerate([stream, third, "captured", null, stream]):
         new = DvlDev(dvl_inputs(1 + step))
@@ -147,7 +142,7 @@ def test_what_is_replayed_as_launches(form):
             # into a stream that is being captured: run at once or with the
             # graph that is captured, as the runtime has it, but always run
             outer = dsv.Graph().capture(lambda: g.replay(third), third)
-            assert direct(outer) == 0
+            assert outer.direct_launches() == 0
             outer.replay(third)
         else:
             g.replay(on)
@@ -206,7 +201,7 @@ def test_no_call_of_another_thread_comes_inside_a_replay(calls):
     d.tokens.fill_(1)
     torch.cuda.synchronize()
     g = dsv.Graph().capture(lambda: [pack(d.tokens, out, mine) for out in packed], stream)
-    assert direct(g) == {1: 1, 6: few(6), 18: 0}[calls]
+    assert g.direct_launches() == {1: 1, 6: few(6), 18: 0}[calls]
     with beside(overwrite):
         for step in range(steps):
             g.replay(stream)
