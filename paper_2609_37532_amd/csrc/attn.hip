@@ -231,17 +231,35 @@ struct Share {
 // (its metadata, page ids and pipeline refill), which at this size is a
 // large part of the kernel.  The cap leaves at most one piece per CU -- a
 // second workgroup on a CU shares its MFMA and LDS with the first and finishes
-// last.  The smallest batches take the smallest cap from two blocks up that
-// does so with at most kMaxMerge pieces to a segment, which the combine kernel
-// loads in one round trip (one request, 716 keys, four layers: 63.1 -> 58.3 us
-// with three blocks instead of eight; 16 pieces to a segment took 70.6 us);
-// the others the smallest of 8 to 12 blocks that fits, else eight, if the
-// pieces fit the grid.  Piece q of n of a `seg`-key segment starts at
-// piece_begin(seg, n, q).
+// last.  The smallest batches take the smallest cap that does so with at most
+// kMaxMerge pieces to a segment, which the combine kernel loads in one round trip
+// (one request, 716 keys, four layers: 63.1 -> 58.3 us with three blocks instead
+// of eight; 16 pieces to a segment took 70.6 us); the others the smallest of 8 to
+// 12 blocks that fits, else eight, if the pieces fit the grid.
+//   A cut costs the combine's round trip and the partials, written and read, so
+// cut_rule bounds the smallest caps by the elements of a segment's partial: the
+// least blocks of a piece, the blocks up to which a segment stays whole, and the
+// pieces, in sixteenths of the CUs.  us a call, D = 128, S segments of b blocks, r
+// rows each: S=64, b=3, r=16 cut 10.4, whole 9.8; b=4 cut 10.2, whole 10.9; b=5, r=64
+// in 192 pieces 14.4, in 128 12.5; S=96, b=4, r=256 in 192 pieces 31.7, whole 21.5.
+// Of caps from two to twelve blocks, over 864 shapes, the rule's is 1.8% off the best
+// in the mean and 27% at most; with the first line for all it was 4.7% and 68%.
+// Piece q of n of a `seg`-key segment starts at piece_begin(seg, n, q).
 constexpr int kNumPieceCaps = 5;
 __device__ __forceinline__ int piece_cap(int c) { return (8 + c) * kBlockKeys; }  // 8..12 blocks
 constexpr int kMaxMerge = 8;
 __device__ __forceinline__ int seg_pieces(int seg, int cap) { return (seg + cap - 1) / cap; }
+struct CutRule {
+  int min_blocks, whole_blocks, cu_sixteenths;
+};
+// Of `total` partial elements over `segs` segments (no division: this is on the way
+// to the first load of every workgroup).
+__device__ __forceinline__ CutRule cut_rule(float total, float segs) {
+  if (total <= 2048.f * segs) return {2, 3, 16};
+  if (total <= 4096.f * segs) return {3, 4, 12};
+  if (total <= 8192.f * segs) return {3, 5, 10};
+  return {3, 5, 5};
+}
 __device__ __forceinline__ int piece_begin(int seg, int n, int q) {
   return (int)((long long)(seg / kBlockKeys) * q / n) * kBlockKeys;
 }
@@ -319,11 +337,12 @@ __device__ __forceinline__ int block_excl_scan(int v, int *lds_tot, int &tot) {
 // Workgroup 0 also publishes the per-request prefixes and the plan for the
 // combine kernel.  LDS use: lds[0..2*NW) scan totals, then the located
 // share.
-template <int NW>
+template <int D, int NW>
 __device__ Share plan_share(const AttnParams &p, int *lds) {
   constexpr int kThreads = NW * kWave;
   const int B = p.num_reqs, tid = threadIdx.x;
   const int per = (B + kThreads - 1) / kThreads;
+  int live = p.cu[B];  // packed rows, in flight with the requests' metadata
   const int lo = min(B, tid * per), hi = min(B, lo + per);
   int sum = 0;
   // with one request per thread (B <= 256) its metadata stays in registers
@@ -341,6 +360,7 @@ __device__ Share plan_share(const AttnParams &p, int *lds) {
     for (int i = lo; i < hi; ++i) sum += segment_len(p, i);
   }
   int total;
+  asm volatile("" : "+v"(live));  // or its load is sunk to its use, a round trip later
   const int excl = block_excl_scan<NW>(sum, lds, total);  // keys before my requests
   int *loc = lds + 2 * NW;  // located share: i, g, off, q0, q1, ctx, start, end
   const int work = total * p.hkv;
@@ -395,10 +415,15 @@ __device__ Share plan_share(const AttnParams &p, int *lds) {
         cap = piece_cap(c);
     // below eight blocks: a cap of c blocks leaves at most work / c pieces
     // plus one per segment
-    const int spare = one_per_cu - pieces[kNumPieceCaps];
-    if (spare > 0) {
-      const int blocks = max(2, max((longest / kBlockKeys + kMaxMerge - 1) / kMaxMerge,
-                                    (work / kBlockKeys + spare - 1) / spare));
+    const int segs = pieces[kNumPieceCaps];
+    // G = 16 at D = 128, on eight waves, counts as the most
+    const CutRule rule = NW == 8 && D == 128
+                             ? CutRule{3, 5, 5}
+                             : cut_rule((float)live * (float)(p.group * p.hkv * D), (float)segs);
+    const int spare = min(p.num_cu * rule.cu_sixteenths / 16, (int)gridDim.x) - segs;
+    if (spare > 0 && longest > rule.whole_blocks * kBlockKeys) {
+      const int blocks = max(rule.min_blocks, max((longest / kBlockKeys + kMaxMerge - 1) / kMaxMerge,
+                                                  (work / kBlockKeys + spare - 1) / spare));
       if (blocks < 8) cap = blocks * kBlockKeys;
     }
   }
@@ -958,7 +983,7 @@ __global__ __launch_bounds__(NW *kWave, min_waves_per_simd(D, NW, kTW)) void att
   __shared__ int ids[kSubPages];
   __shared__ int lds_plan[2 * NW + 8 + (kNumPieceCaps / 2 + 2) * NW];
 
-  const Share sh = plan_share<NW>(p, lds_plan);
+  const Share sh = plan_share<D, NW>(p, lds_plan);
   if (sh.start >= sh.end) return;
   int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   int lane = threadIdx.x % kWave;

@@ -64,3 +64,14 @@ def test_mixed_tiles_in_one_share(group):
     qlens = [int(k) for k in rng.integers(1, 17, size=48)]
     ctx = [int(c) for c in rng.integers(200, 2600, size=48)]
     check("G=%d mixed" % group, 7 + group, ctx, qlens, 4 * group, 4, 128)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("group,k", [(1, 16), (2, 16), (4, 8), (4, 16), (8, 16), (16, 4), (16, 16)])
+@pytest.mark.parametrize("reqs,hkv", [(1, 2), (6, 8)])
+def test_small_batch_pieces(reqs, hkv, group, k, d):
+    # segments of two to nine blocks, about where the smallest batches begin to cut
+    for blocks in (2, 3, 4, 5, 6, 9):
+        ctx = [32 * blocks - k - i % 3 for i in range(reqs)]
+        check("pieces G=%d k=%d d=%d %d x %d, %d blocks" % (group, k, d, reqs, hkv, blocks),
+              31 * blocks + group, ctx, [k] * reqs, group * hkv, hkv, d)
