@@ -48,8 +48,9 @@
 //  * Waves of a workgroup split the dims when a request has one or two row
 //    tiles; beyond that each wave owns one to four tiles, so that every piece
 //    reads its K and V once: four waves hold the eight tiles of eight query
-//    heads to a KV head and a full block, and at D = 64 the sixteen of G = 16,
-//    which eight waves hold at D = 128.
+//    heads to a KV head and a full block, eight waves, or at D = 64 also four, the
+//    sixteen of G = 16.  Only many short segments at G = 16, D = 128, take two
+//    passes of K and V, from cache.
 //  * The workgroups placed after the first on a CU run at raised wave priority
 //    over half of their share, so that a CU's workgroups finish together.
 //
@@ -248,7 +249,6 @@ struct Share {
 constexpr int kNumPieceCaps = 5;
 __device__ __forceinline__ int piece_cap(int c) { return (8 + c) * kBlockKeys; }  // 8..12 blocks
 constexpr int kMaxMerge = 8;
-__device__ __forceinline__ int seg_pieces(int seg, int cap) { return (seg + cap - 1) / cap; }
 struct CutRule {
   int min_blocks, whole_blocks, cu_sixteenths;
 };
@@ -260,6 +260,7 @@ __device__ __forceinline__ CutRule cut_rule(float total, float segs) {
   if (total <= 8192.f * segs) return {3, 5, 10};
   return {3, 5, 5};
 }
+__device__ __forceinline__ int seg_pieces(int seg, int cap) { return (seg + cap - 1) / cap; }
 __device__ __forceinline__ int piece_begin(int seg, int n, int q) {
   return (int)((long long)(seg / kBlockKeys) * q / n) * kBlockKeys;
 }
@@ -341,8 +342,8 @@ template <int D, int NW>
 __device__ Share plan_share(const AttnParams &p, int *lds) {
   constexpr int kThreads = NW * kWave;
   const int B = p.num_reqs, tid = threadIdx.x;
-  const int per = (B + kThreads - 1) / kThreads;
   int live = p.cu[B];  // packed rows, in flight with the requests' metadata
+  const int per = (B + kThreads - 1) / kThreads;
   const int lo = min(B, tid * per), hi = min(B, lo + per);
   int sum = 0;
   // with one request per thread (B <= 256) its metadata stays in registers
@@ -359,8 +360,8 @@ __device__ Share plan_share(const AttnParams &p, int *lds) {
 #pragma unroll 4
     for (int i = lo; i < hi; ++i) sum += segment_len(p, i);
   }
-  int total;
   asm volatile("" : "+v"(live));  // or its load is sunk to its use, a round trip later
+  int total;
   const int excl = block_excl_scan<NW>(sum, lds, total);  // keys before my requests
   int *loc = lds + 2 * NW;  // located share: i, g, off, q0, q1, ctx, start, end
   const int work = total * p.hkv;
@@ -918,11 +919,11 @@ __device__ __forceinline__ void write_rows(const AttnParams &p, const Piece &x, 
 // itself.
 template <int D, int TW, int NE, int NW>
 __device__ __forceinline__ void run_piece(const AttnParams &p, char *buf, int *ids, const Piece &x,
-                                          int wave, int lane) {
+                                          int wave, int lane, int first_tile = 0) {
   using R = Ring<D, NW>;
   constexpr int kParts = D / 16 / NE;  // waves to a tile
   Role role;
-  role.tile0 = wave / kParts * TW;
+  role.tile0 = first_tile + wave / kParts * TW;
   role.e_lo = wave % kParts * NE;
   role.active = role.tile0 * 16 < p.group * x.rq.k;
   RowState<TW, NE> st;
@@ -963,21 +964,17 @@ __device__ __forceinline__ void run_piece(const AttnParams &p, char *buf, int *i
 }
 
 // NW waves, each with up to kTW row tiles: as many as the group's largest
-// requests have (16 rows of each head).  Workgroups to a CU, by registers: two
-// of four waves at D = 128 (three measured slower: 36 requests, contexts to 2K,
-// four layers 232.8 -> 252.9 us) and one of eight (G = 16).  At D = 64 a step is half
-// the bytes and a wave needs half the registers: four workgroups with one tile to a
-// wave, three with two (four would spill): 16 requests of 10K keys on one KV head
-// take 22.5 us instead of 26.4, 33 short ones of eight heads to a KV head 39.5
-// instead of 43.5.  And two with four tiles (G = 16), where eight waves to a lone
-// workgroup keep few of them busy on short requests: 32 requests, contexts to 8K,
-// 16 heads on each of 8 KV heads, one row each 75.0 -> 64.4 us, lengths of a
-// geometric distribution 156.6 -> 107.0, full blocks 165 -> 150; 8 full blocks to
-// 2K lose 28.4 -> 30.5, 4 requests of 6 rows to 16K 34.8 -> 38.5.
+// requests have (16 rows of each head), or as many at a time, K and V read again for
+// the rest (kPasses).  Workgroups to a CU, by registers: two of four waves at
+// D = 128 (three measured slower: 36 requests, contexts to 2K, four layers 232.8 ->
+// 252.9 us), one of eight.  At D = 64 a step is half the bytes and a wave needs half
+// the registers: four with one tile to a wave, three with two (four would spill), two
+// with four: 16 requests of 10K keys on one KV head take 22.5 us instead of 26.4, 33
+// short ones of eight heads to a KV head 39.5 instead of 43.5.
 constexpr int min_waves_per_simd(int D, int NW, int kTW) {
   return D == 64 && NW == 4 ? (kTW == 1 ? 4 : (kTW == 2 ? 3 : 2)) : 2;
 }
-template <int D, int NW, int kTW>
+template <int D, int NW, int kTW, bool kPasses = false>
 __global__ __launch_bounds__(NW *kWave, min_waves_per_simd(D, NW, kTW)) void attn_streamk_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(1024))) char buf[Ring<D, NW>::kBytes];
   __shared__ int ids[kSubPages];
@@ -1041,6 +1038,11 @@ __global__ __launch_bounds__(NW *kWave, min_waves_per_simd(D, NW, kTW)) void att
         run_piece<D, 2, kBlocks, NW>(p, buf, ids, x, wave, lane);
       else
         run_piece<D, 4, kBlocks, NW>(p, buf, ids, x, wave, lane);
+    } else if constexpr (kPasses) {
+      for (int t = 0; t < nt; t += kTW * NW) {
+        if (t > 0) __syncthreads();  // the last pass's LDS has been read
+        run_piece<D, kTW, kBlocks, NW>(p, buf, ids, x, wave, lane, t);
+      }
     } else if constexpr (kTW == 2)
       run_piece<D, 2, kBlocks, NW>(p, buf, ids, x, wave, lane);
 
@@ -1201,34 +1203,62 @@ int device_cus() {
   return cus;
 }
 
-// The split kernel for a head dim and GQA group, and its threads.
+// The split kernel for a batch's dims, and its threads.  Only G = 16, with up to
+// sixteen row tiles to a request, has a choice, between eight waves in one workgroup
+// to a CU and forms with more, smaller workgroups; of what it depends on the host
+// knows the most segments (requests x KV heads) and the longest context.
+//  D = 128: eight waves hold all tiles.  Where there are more segments than CUs and
+//   each is short, that leaves every CU several in a row to start: four waves
+//   there, eight tiles at a time, the second pass's K and V from cache (64 requests
+//   to 200 keys, 8 KV heads, one row each 46.3 -> 33.9 us, full blocks 68.8 -> 53.1; to
+//   500 keys 54.8 -> 51.5 and 89.8 -> 102.9).
+//  D = 64: four waves can hold all tiles, two workgroups to a CU, which pays with
+//   many segments (us, eight waves / four: 32 requests to 8K, 8 KV heads, one row each
+//   75.0 / 64.4, geometric lengths 156.6 / 107.0, full blocks 165 / 150; 24 to 6K, 4 KV
+//   heads 28.9 / 26.1, 52.7 / 42.9, 59.1 / 61.5); with few the second workgroup only
+//   adds partials (1 to 30K, 8 KV heads 23.3 / 27.9, full blocks 46.9 / 59.0; 64 to
+//   4K, 1 KV head, full blocks 38.7 / 42.6).
 struct SplitKernel {
   void (*fn)(AttnParams);
   int threads;
 };
-SplitKernel split_kernel(int head_dim, int group) {
-  constexpr int k4 = 4 * kWave, k8 = 8 * kWave;
-  if (head_dim == 128) {
-    if (group > 8) return {attn_streamk_kernel<128, 8, 2>, k8};
-    if (group > 4) return {attn_streamk_kernel<128, 4, 2>, k4};
-    return {attn_streamk_kernel<128, 4, 1>, k4};
+constexpr int kSplitKernels = 8;
+constexpr int kManySegments128 = 256, kShortKeys = 256, kManySegments64 = 64;
+int split_kernel_index(const dsv_attn_dims &d) {
+  const int group = d.num_q_heads / d.num_kv_heads;
+  const long long segments = (long long)d.num_reqs * d.num_kv_heads;
+  if (d.head_dim == 128) {
+    if (group > 8) return segments > kManySegments128 && d.max_kv_len <= kShortKeys ? 3 : 2;
+    return group > 4 ? 1 : 0;
   }
-  if (group > 8) return {attn_streamk_kernel<64, 4, 4>, k4};
-  if (group > 4) return {attn_streamk_kernel<64, 4, 2>, k4};
-  return {attn_streamk_kernel<64, 4, 1>, k4};
+  if (group > 8) return segments > kManySegments64 ? 7 : 6;
+  return group > 4 ? 5 : 4;
+}
+SplitKernel split_kernel(int index) {
+  constexpr int k4 = 4 * kWave, k8 = 8 * kWave;
+  switch (index) {
+    case 0: return {attn_streamk_kernel<128, 4, 1>, k4};
+    case 1: return {attn_streamk_kernel<128, 4, 2>, k4};
+    case 2: return {attn_streamk_kernel<128, 8, 2>, k8};
+    case 3: return {attn_streamk_kernel<128, 4, 2, true>, k4};
+    case 4: return {attn_streamk_kernel<64, 4, 1>, k4};
+    case 5: return {attn_streamk_kernel<64, 4, 2>, k4};
+    case 6: return {attn_streamk_kernel<64, 8, 2>, k8};
+    default: return {attn_streamk_kernel<64, 4, 4>, k4};
+  }
 }
 
 // Workgroups the GPU holds at once for the split kernel (cached per device
 // and kernel; a host query, so it is safe during graph capture).
-int resident_workgroups(int head_dim, int group) {
-  static int cache[64][6];
+int resident_workgroups(int index) {
+  static int cache[64][kSplitKernels];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
-  int &slot = cache[dev][(head_dim == 128 ? 1 : 0) + (group > 8 ? 4 : (group > 4 ? 2 : 0))];
+  int &slot = cache[dev][index];
   if (slot > 0) return slot;
   const int cus = device_cus();
   int per_cu = 0;
-  const SplitKernel k = split_kernel(head_dim, group);
+  const SplitKernel k = split_kernel(index);
   const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
       &per_cu, reinterpret_cast<const void *>(k.fn), k.threads, 0);
   if (e != hipSuccess || cus <= 0 || per_cu <= 0) return 0;
@@ -1241,7 +1271,8 @@ int resident_workgroups(int head_dim, int group) {
 // Upper bound of the persistent grid, known without a device: at most 1024
 // workgroups and never more than the 32-key blocks the largest batch could hold.
 // The workspace is sized for it.  A 256-CU MI355X holds at once, by head_dim and
-// group: 128, up to 8: 512; 128, 16: 256; 64, up to 4: 1024; 64, 8: 768; 64, 16: 512.
+// group: 128, up to 8: 512; 128, 16: 256 (512 of the form for many short segments);
+// 64, up to 4: 1024; 64, 8: 768; 64, 16: 512 (256 of the form for few segments).
 int32_t attn_grid_cap(const dsv_attn_dims &d) {
   constexpr long long kMaxGrid = 1024;
   const long long blocks = (long long)d.num_reqs * d.num_kv_heads *
@@ -1253,7 +1284,7 @@ int32_t attn_num_cu() { return device_cus(); }
 
 // Launch grid: the workgroups the current device holds at once, capped.
 int32_t attn_grid(const dsv_attn_dims &d) {
-  const int r = resident_workgroups(d.head_dim, d.num_q_heads / d.num_kv_heads);
+  const int r = resident_workgroups(split_kernel_index(d));
   if (r <= 0) return 0;
   const int32_t cap = attn_grid_cap(d);
   return r < cap ? r : cap;
@@ -1271,17 +1302,17 @@ AttnWorkspace attn_workspace_layout(const dsv_attn_dims &d) {
   return w;
 }
 
-hipError_t launch_verify_attn(const AttnParams &p, int head_dim, hipStream_t s) {
+hipError_t launch_verify_attn(const AttnParams &p, const dsv_attn_dims &d, hipStream_t s) {
   // rows of one request and KV head: G * k_i <= G * 16
-  const int comb_rows = head_dim == 128 ? kCombThreads / 32 : kCombThreads / 16;
+  const int comb_rows = d.head_dim == 128 ? kCombThreads / 32 : kCombThreads / 16;
   const dim3 grid_comb((p.group * kMaxQlen + comb_rows - 1) / comb_rows, p.hkv,
                        p.num_reqs + 1);
   timing_mark(kTimeAttnSplit, false, s);
-  const SplitKernel split = split_kernel(head_dim, p.group);
+  const SplitKernel split = split_kernel(split_kernel_index(d));
   launch_kernel(split.fn, dim3(p.num_wg), dim3(split.threads), s, p);
   timing_mark(kTimeAttnSplit, true, s);
   timing_mark(kTimeAttnCombine, false, s);
-  if (head_dim == 128)
+  if (d.head_dim == 128)
     launch_kernel(attn_combine_kernel<128>, grid_comb, dim3(kCombThreads), s, p);
   else
     launch_kernel(attn_combine_kernel<64>, grid_comb, dim3(kCombThreads), s, p);

@@ -59,7 +59,7 @@ struct AttnWorkspace {
 int32_t attn_grid(const dsv_attn_dims &d);  // launch grid on the current device
 int32_t attn_num_cu();                      // compute units of the current device
 AttnWorkspace attn_workspace_layout(const dsv_attn_dims &d);
-hipError_t launch_verify_attn(const AttnParams &p, int head_dim, hipStream_t s);
+hipError_t launch_verify_attn(const AttnParams &p, const dsv_attn_dims &d, hipStream_t s);
 
 // -------------------------------------------------------------------------
 // acceptance

@@ -66,6 +66,17 @@ def test_mixed_tiles_in_one_share(group):
     check("G=%d mixed" % group, 7 + group, ctx, qlens, 4 * group, 4, 128)
 
 
+@pytest.mark.parametrize("hi", [60, 240])
+@pytest.mark.parametrize("d,reqs,hkv", [(128, 65, 4), (128, 64, 4), (64, 33, 2), (64, 32, 2)])
+def test_many_short_segments_of_sixteen_heads(d, reqs, hkv, hi):
+    # to either side of the segment counts (256 and 64) at which a batch of sixteen heads
+    # to a KV head changes its kernel, every tile count among the requests
+    rng = np.random.default_rng(reqs + hi)
+    qlens = [1 + i % 16 for i in range(reqs)]
+    ctx = [int(c) for c in rng.integers(0, hi - 16, size=reqs)]
+    check("G=16 d=%d %d x %d to %d" % (d, reqs, hkv, hi), 900 + reqs, ctx, qlens, 16 * hkv, hkv, d)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("group,k", [(1, 16), (2, 16), (4, 8), (4, 16), (8, 16), (16, 4), (16, 16)])
 @pytest.mark.parametrize("reqs,hkv", [(1, 2), (6, 8)])
