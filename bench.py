@@ -731,7 +731,7 @@ def main():
         },
         "roofline": {
             "bound": "hbm",
-            "kernel": "attn_streamk_kernel<128, 4, 1>",
+            "kernel": "attn_streamk_kernel<128, 4, 1, false>",
             "achieved": round(achieved, 1),
             "peak": HBM_PEAK_GBPS,
             "unit": "GB/s",
