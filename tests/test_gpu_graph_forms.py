@@ -192,17 +192,21 @@ def test_no_call_of_another_thread_comes_inside_a_replay(calls):
         dsv.dvl_allocate_pack(d.logits, d.num_live, tokens, d.positions, d.kv_refs, o[0], o[1],
                               into, o[2], o[3], stream=stream)
 
+    started = threading.Event()
+
     def overwrite(stopped):
         for n in range(100_000):
             if stopped():
                 break
             pack(ones[n % 2], half, theirs)
+            started.set()
 
     d.tokens.fill_(1)
     torch.cuda.synchronize()
     g = dsv.Graph().capture(lambda: [pack(d.tokens, out, mine) for out in packed], stream)
     assert g.direct_launches() == {1: 1, 6: few(6), 18: 0}[calls]
     with beside(overwrite):
+        started.wait(30)
         for step in range(steps):
             g.replay(stream)
             with torch.cuda.stream(stream):
